@@ -33,12 +33,13 @@ struct DevPat {
   const int32_t* sr_pos;    // [nnz]        W slot of CSR entry j
   const int32_t* sc_off;    // [ceil(P/64)] first slot of each OD slice
   const int32_t* sc_row;    // [sc_len]     link of each WT slot
-  const int32_t* sc_pos;    // [nnz]        WT slot of CSC entry jj
 };
 
 // Device view of the value arrays of all clusters.
 //   W : sliced by link [C][K][T][sr_len]
 //   WT: sliced by OD   [C][K][T][sc_len]
+//   PR, PC: packed by union tile, of links [C][K][T][pr_len] and of ODs
+//   [C][K][T][pc_len] (DevUnion)
 //   scale (FP8 only): [C][K][T][n_ptile], one float per 64-OD column tile
 struct DevVals {
   const void* W;
@@ -47,6 +48,9 @@ struct DevVals {
   int64_t cstride_r;     // K*T*sr_len
   int64_t cstride_c;     // K*T*sc_len
   int32_t n_ptile;       // ceil(P/64)
+  const void* PR;
+  const void* PC;
+  int64_t pr_len, pc_len;
 };
 
 // Forward link tiles come in groups of kFwdTileGroup that share one OD range
@@ -77,6 +81,23 @@ struct DevTiles {
   const void* Gc = nullptr;
 };
 
+// Tiles of the pattern for the kernels of several days (unions.hip): 16 lines
+// (links of W, ODs of WT) by the union of their columns, in runs of 16.
+//   line[16 n_tiles]   line of each tile row (-1 past the last)
+//   run[4 n_tiles]     1 when rows 4k..4k+3 are consecutive lines of one
+//                      aligned block of four
+//   off[n_tiles + 1]   first column run of each tile
+//   col[16 per run]    the columns; run r, product j, lane group g: col[16r + 4g + j]
+// The values of an (l, t) block are stored in operand order, 256 per run:
+// 4 consecutive ones per lane, one per product (DevVals::PR, PC).
+struct DevUnion {
+  int32_t n_tiles = 0;
+  const int32_t* line = nullptr;
+  const int32_t* run = nullptr;
+  const int32_t* off = nullptr;
+  const int32_t* col = nullptr;
+};
+
 struct dode_dar {
   dode_dims dims{};
   int32_t C = 0;
@@ -87,7 +108,6 @@ struct dode_dar {
   int32_t* d_col = nullptr;
   int32_t* d_col_ptr = nullptr;
   int32_t* d_row = nullptr;
-  int32_t* d_csc2csr = nullptr;   // CSC slot -> CSR slot
   int32_t* d_row_of_nz = nullptr; // link of CSR slot j
   int64_t sr_len = 0, sc_len = 0;   // sliced value layouts (see DevPat)
   int32_t* d_sr_first = nullptr;
@@ -95,33 +115,41 @@ struct dode_dar {
   int32_t* d_sr_pos = nullptr;
   int32_t* d_sc_off = nullptr;
   int32_t* d_sc_row = nullptr;
-  int32_t* d_sc_pos = nullptr;
   void* d_W = nullptr;
   void* d_WT = nullptr;
   float* d_scale = nullptr;
   int64_t device_bytes = 0;
   std::vector<int32_t> h_row_ptr, h_col, h_col_ptr, h_row, h_csc2csr;
+  DevUnion u_rows, u_cols;   // tiles of links and of ODs
+  // packed values of the union tiles (nullptr: the one-day kernels run, see
+  // kUnionClusters in api.hip)
+  int64_t pr_len = 0, pc_len = 0;
+  void* d_PR = nullptr;
+  void* d_PC = nullptr;
+  int32_t* d_u_rows = nullptr;
+  int32_t* d_u_cols = nullptr;
   // MFMA tile layout (BF16 / FP8 storage only)
   bool has_tiles = false;
   DevTiles tiles;
   int32_t* d_tile_meta = nullptr;   // f_plo | f_ks | f_koff | g_alo | g_ks | g_koff
   std::vector<int32_t> h_tile_meta; // host copy
-  int32_t* d_posf = nullptr;        // [nnz] element offset of CSR slot j in a forward block
-  int32_t* d_posg = nullptr;        // [nnz] element offset of CSC slot jj in an adjoint block
+  // W slot of every WT slot, packed union value and tile element of a block,
+  // in the order WT, PR, PC, Fv, Gv (-1: padding)
+  int32_t* d_code_of = nullptr;
   void* d_Fv = nullptr;
   void* d_Gv = nullptr;
   void* d_Fc = nullptr;             // correction tiles (FP8 with DODE_DAR_CORRECTION)
   void* d_Gc = nullptr;
   bool has_corr = false;
-  std::vector<int32_t> h_posf, h_posg;
+  std::vector<int32_t> h_posf, h_posg;  // tile element of CSR slot j / CSC slot jj of a block
 
   DevPat pat() const {
     return DevPat{dims.P, dims.L, dims.T, dims.H, dims.K, nnz, d_row_ptr, d_col, d_col_ptr, d_row,
-                  sr_len, sc_len, d_sr_first, d_sr_col, d_sr_pos, d_sc_off, d_sc_row, d_sc_pos};
+                  sr_len, sc_len, d_sr_first, d_sr_col, d_sr_pos, d_sc_off, d_sc_row};
   }
   DevVals vals() const {
     return DevVals{d_W, d_WT, d_scale, (int64_t)dims.K * dims.T * sr_len,
-                   (int64_t)dims.K * dims.T * sc_len, (dims.P + 63) / 64};
+                   (int64_t)dims.K * dims.T * sc_len, (dims.P + 63) / 64, d_PR, d_PC, pr_len, pc_len};
   }
 };
 
@@ -321,6 +349,14 @@ std::vector<WaveWork> work_table(const dode_dar* dar, const std::vector<int32_t>
                                  const std::vector<int32_t>& gf, const std::vector<int32_t>& gn,
                                  bool fwd, int32_t rows, bool tile_major, bool group_fastest);
 
+// Day groups of the pattern kernels (days_kernels.hip): groups of up to nd
+// consecutive days of one cluster, from a table (cluster | first | count, n
+// each) or, with tab == nullptr, days 0..n_days-1 of `cluster`.
+struct DayList {
+  const int32_t* tab;
+  int32_t n, nd, cluster, n_days;
+};
+
 // Zeroed elements past the end of each plan state array (X, Q, A, R).
 constexpr int64_t kStatePad = 64;
 
@@ -393,6 +429,9 @@ struct dode_plan {
   double* d_loss = nullptr;       // [D] loss of the plan's days (plan order)
   int32_t* d_order = nullptr;     // [D] caller day of plan day i (days grouped by cluster)
   Layout ly{};                    // plan layout of X, Q, A, R
+  int32_t* d_days = nullptr;      // DayList table of the pattern kernels (nd > 1)
+  DayList days{};
+  bool step_days = false;         // minibatches of an FP32 / FP64 plan in day groups
   int32_t* d_groups = nullptr;    // cluster | first | count | cbase | cgroups (n_groups each)
   int32_t n_groups = 0;
   int32_t day_tile = 32;          // days per group
@@ -519,6 +558,32 @@ hipError_t plain_apply_rows(const dode_dar* dar, const int32_t* day_cluster, int
 hipError_t plain_adjoint_rows(const dode_dar* dar, const int32_t* day_cluster, int32_t cluster,
                               const Layout& ly, const void* R, void* G, int32_t n_days,
                               hipStream_t s);
+// ---- matrix-core kernels of the pattern form (days_kernels.hip) ---------
+// Host form of a DevUnion, all arrays in one buffer: n_lines lines with sorted
+// columns ptr/idx of n_cols, slot of each entry (unions.hip).
+struct HostUnion {
+  int32_t n_tiles = 0;
+  std::vector<int32_t> buf;       // line | run | col | off
+  std::vector<int32_t> code_of;   // slot of every packed value of a block (-1: padding)
+  DevUnion at(const int32_t* p) const;
+};
+HostUnion build_union(int32_t n_lines, int32_t n_cols, const std::vector<int32_t>& ptr,
+                      const std::vector<int32_t>& idx, const std::vector<int32_t>& slot, bool f64);
+// days per group for clusters of up to n_days days: 1 = use the one-day kernels
+int32_t days_per_group(const dode_dar* dar, int32_t n_days);
+// rows of cs (nullptr: every interval): out = rho Q (- X if X), in the R layout
+// for a minibatch and the X layout for whole days; part (nullable, whole days)
+// = [n][H] row sums of squares
+hipError_t days_rows(const dode_dar* dar, const DayList& dl, const ChunkSched* cs, int32_t n_rows,
+                     const Layout& ly, const void* Q, const void* X, void* out, double* part,
+                     hipStream_t s);
+// G (Q layout) = f * rho^T R for full residual rows R
+hipError_t days_cols(const dode_dar* dar, const DayList& dl, const Layout& ly, const void* R,
+                     void* G, double f, hipStream_t s);
+// adjoint and step of a minibatch
+hipError_t days_cols_step(const dode_dar* dar, const DayList& dl, const ChunkSched& cs,
+                          const Layout& ly, const void* R, void* Q, void* A, const StepArgs& sa,
+                          hipStream_t s);
 // plan state copies: plan entry (day i, row r, col k) at i*sd + r*sr + col_at(k, sb)
 // = src[order[i]][r][k] (gather) and back (scatter); clamp projects onto >= 0
 // on the way in
@@ -596,10 +661,14 @@ hipError_t mfma_epoch_persistent(const dode_dar* dar, const PersistMinibatch* mb
 hipError_t mfma_minibatch(const dode_dar* dar, const CompSched& ks, const DayGroups& dg,
                           const Layout& ly, const float* X, float* R, float* Q, float* A,
                           const StepArgs& st, hipStream_t s);
-// host: tile layout (ranges, positions, device arrays), then each cluster's
-// entries from its pattern-form codes (CSR order, storage type) (tiles.hip)
+// Every device copy of one cluster's values (W, WT, packed values, tiles) from
+// W_state (dev [K][T][nnz], state type, rounded to the storage type), or, when
+// W_state is nullptr, the others from the codes in W (value_kernels.hip)
+hipError_t install_values(const dode_dar* dar, int32_t cluster, const void* W_state,
+                          hipStream_t s);
+// host: tile layout (ranges, positions) and the device arrays, filled by
+// install_values (tiles.hip)
 dode_status tiles_prepare(dode_dar* d, std::string& err);
-dode_status tiles_fill_cluster(dode_dar* d, int32_t c, const void* codes_csr, std::string& err);
 // bf16 correction codes of one cluster (CSR order) into the correction tiles
 dode_status tiles_fill_correction(dode_dar* d, int32_t c, const uint16_t* corr_csr,
                                   std::string& err);
@@ -616,8 +685,6 @@ hipError_t routes_logits_bwd(const DevRoutes& r, bool f64, const void* Rr, const
 hipError_t loss_bwd_dW(const dode_dar* dar, const void* R, const void* Q, int32_t n_days,
                        double scale, void* dW, hipStream_t s);
 hipError_t scale_state(bool f64, void* x, int64_t n, double f, hipStream_t s);
-// copy the pattern-form codes of one cluster into its MFMA tiles (after quantize_values)
-hipError_t update_tiles(const dode_dar* dar, int32_t cluster, hipStream_t s);
 
 // ---- small generic kernels (plain_kernels.hip) -------------------------
 hipError_t sum_partials(const double* part, int32_t n_per, int32_t n_days, double* out,
@@ -633,8 +700,6 @@ hipError_t r2_finish(const double* loss, const double* sst, int32_t n_days, doub
                      hipStream_t s);
 hipError_t check_finite(bool f64, const void* X, int64_t n, int32_t* flag, hipStream_t s);
 hipError_t clamp_nonneg(bool f64, void* Q, int64_t n, hipStream_t s);
-hipError_t quantize_values(const dode_dar* dar, int32_t cluster, const void* W_state,
-                           hipStream_t s);
 
 // ---- number formats (host side, exact round-to-nearest-even) -----------
 uint16_t host_f64_to_bf16(double v);

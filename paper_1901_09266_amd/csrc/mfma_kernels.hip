@@ -804,41 +804,7 @@ k_epoch_persistent(DevPat pt, DevTiles tl, const PersistMinibatch* __restrict__ 
   }
 }
 
-// Copy the pattern-form codes of one (cluster, l, t) block (link-sliced, just
-// rewritten by the quantisation kernel) into its packed tiles.
-template <typename E>
-__global__ void __launch_bounds__(256)
-k_update_tiles(DevPat pt, DevTiles tl, int32_t c, const E* __restrict__ codes,
-               const int32_t* __restrict__ posf, const int32_t* __restrict__ posg,
-               const int32_t* __restrict__ csc2csr, E* __restrict__ F, E* __restrict__ G) {
-  const int64_t lt = blockIdx.x;
-  const int l = (int)(lt / pt.T), t = (int)(lt % pt.T);
-  if (t + l >= pt.H) return;   // block never read
-  const int64_t blk = (int64_t)c * pt.K * pt.T + lt;
-  const E* w = codes + blk * pt.sr_len;   // link-sliced codes
-  E* f = F + blk * tl.kf_total * 512;
-  E* g = G + blk * tl.kg_total * 512;
-  for (int64_t j = threadIdx.x; j < pt.nnz; j += blockDim.x) f[posf[j]] = w[pt.sr_pos[j]];
-  for (int64_t jj = threadIdx.x; jj < pt.nnz; jj += blockDim.x)
-    g[posg[jj]] = w[pt.sr_pos[csc2csr[jj]]];
-}
-
 }  // namespace
-
-hipError_t update_tiles(const dode_dar* dar, int32_t cluster, hipStream_t s) {
-  const dim3 grid(dar->dims.K * dar->dims.T);
-  if (dar->storage == DODE_FP8_E4M3)
-    hipLaunchKernelGGL(k_update_tiles<uint8_t>, grid, dim3(256), 0, s, dar->pat(), dar->tiles,
-                       cluster, static_cast<const uint8_t*>(dar->d_W), dar->d_posf, dar->d_posg,
-                       dar->d_csc2csr, static_cast<uint8_t*>(dar->d_Fv),
-                       static_cast<uint8_t*>(dar->d_Gv));
-  else
-    hipLaunchKernelGGL(k_update_tiles<uint16_t>, grid, dim3(256), 0, s, dar->pat(), dar->tiles,
-                       cluster, static_cast<const uint16_t*>(dar->d_W), dar->d_posf, dar->d_posg,
-                       dar->d_csc2csr, static_cast<uint16_t*>(dar->d_Fv),
-                       static_cast<uint16_t*>(dar->d_Gv));
-  return hipGetLastError();
-}
 
 template <int MODE, int NT>
 hipError_t launch_fwd(const dode_dar* dar, const ChunkSched& cs, const WaveWork* wt, int64_t n,

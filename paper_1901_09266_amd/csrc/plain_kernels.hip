@@ -7,7 +7,7 @@
 //   chunk_adj_step: g = rho_o^T r, then Adagrad / fixed step and max(q, 0),
 //                   fused, for every departure interval the minibatch reaches.
 #include "dode_internal.h"
-#include "numfmt.h"
+#include "pattern_dot.h"
 
 #include <cmath>
 
@@ -17,86 +17,6 @@ constexpr int kRowsBlock = 256;
 constexpr int kColsBlock = 64;
 constexpr int kRedBlock = 256;
 constexpr size_t kQStageBytes = 32768;   // demand rows staged in LDS by the forward
-
-// ---------------------------------------------------------------- values --
-__device__ __forceinline__ float bf16_bits_to_f32(uint16_t b) {
-  return __uint_as_float(static_cast<uint32_t>(b) << 16);
-}
-
-// OCP E4M3FN: 1 sign, 4 exponent bits (bias 7), 3 mantissa bits; exponent
-// field 0 is subnormal (m * 2^-9); the all-ones code is NaN (never stored).
-__device__ __forceinline__ float e4m3_bits_to_f32(uint8_t b) {
-  const uint32_t e = (b >> 3) & 0xF, m = b & 7;
-  float v = e == 0 ? static_cast<float>(m) * 0x1p-9f : __uint_as_float(((e + 120u) << 23) | (m << 20));
-  return (b & 0x80) ? -v : v;
-}
-
-template <int ST>
-struct Load;
-template <>
-struct Load<DODE_F64> {
-  __device__ static double get(const void* W, int64_t i, const float*, int64_t) {
-    return static_cast<const double*>(W)[i];
-  }
-};
-template <>
-struct Load<DODE_F32> {
-  __device__ static float get(const void* W, int64_t i, const float*, int64_t) {
-    return static_cast<const float*>(W)[i];
-  }
-};
-template <>
-struct Load<DODE_BF16> {
-  __device__ static float get(const void* W, int64_t i, const float*, int64_t) {
-    return bf16_bits_to_f32(static_cast<const uint16_t*>(W)[i]);
-  }
-};
-template <>
-struct Load<DODE_FP8_E4M3> {
-  __device__ static float get(const void* W, int64_t i, const float* scale, int64_t si) {
-    return e4m3_bits_to_f32(static_cast<const uint8_t*>(W)[i]) * scale[si];
-  }
-};
-
-// Two neighbouring values i, i+1 (i even) with one load.
-template <int ST>
-struct Load2;
-template <>
-struct Load2<DODE_F64> {
-  __device__ static void get(const void* W, int64_t i, const float*, int64_t, int64_t, double& w0,
-                             double& w1) {
-    const double2 v = *reinterpret_cast<const double2*>(static_cast<const double*>(W) + i);
-    w0 = v.x;
-    w1 = v.y;
-  }
-};
-template <>
-struct Load2<DODE_F32> {
-  __device__ static void get(const void* W, int64_t i, const float*, int64_t, int64_t, float& w0,
-                             float& w1) {
-    const float2 v = *reinterpret_cast<const float2*>(static_cast<const float*>(W) + i);
-    w0 = v.x;
-    w1 = v.y;
-  }
-};
-template <>
-struct Load2<DODE_BF16> {
-  __device__ static void get(const void* W, int64_t i, const float*, int64_t, int64_t, float& w0,
-                             float& w1) {
-    const uint32_t b = *reinterpret_cast<const uint32_t*>(static_cast<const uint16_t*>(W) + i);
-    w0 = bf16_bits_to_f32(static_cast<uint16_t>(b & 0xFFFFu));
-    w1 = bf16_bits_to_f32(static_cast<uint16_t>(b >> 16));
-  }
-};
-template <>
-struct Load2<DODE_FP8_E4M3> {
-  __device__ static void get(const void* W, int64_t i, const float* scale, int64_t si0, int64_t si1,
-                             float& w0, float& w1) {
-    const uint16_t b = *reinterpret_cast<const uint16_t*>(static_cast<const uint8_t*>(W) + i);
-    w0 = e4m3_bits_to_f32(static_cast<uint8_t>(b & 0xFFu)) * scale[si0];
-    w1 = e4m3_bits_to_f32(static_cast<uint8_t>(b >> 8)) * scale[si1];
-  }
-};
 
 __device__ __forceinline__ int day_cl(const int32_t* day_cluster, int32_t cluster, int d) {
   return day_cluster ? day_cluster[d] : cluster;
@@ -121,98 +41,6 @@ __device__ double block_max(double v, double* sh) {
     __syncthreads();
   }
   return sh[0];
-}
-
-// Row (h, a) of rho_c applied to q_d:  sum_l sum_{p in row a} W[l][h-l][a,p] q[h-l][p].
-// The row's entries are taken in CSR order from the link-sliced layout, where
-// they come in pairs: one load brings two values (and one their two ODs), and
-// the loads of four entries are issued together (the sums keep their order).
-template <int ST, typename S>
-__device__ __forceinline__ S row_dot(const DevPat& pt, const DevVals& v, int c, int h, int a,
-                                     const S* q, int64_t q_t, int64_t q_b) {
-  S acc = 0;
-  const int32_t deg = pt.row_ptr[a + 1] - pt.row_ptr[a];
-  const int32_t s0 = pt.sr_first[a];
-  for (int l = 0; l < pt.K; ++l) {
-    const int t = h - l;
-    if (t < 0) break;
-    if (t >= pt.T) continue;
-    const int64_t base = c * v.cstride_r + ((int64_t)l * pt.T + t) * pt.sr_len;
-    const int64_t sbase = (c * (int64_t)pt.K * pt.T + (int64_t)l * pt.T + t) * v.n_ptile;
-    const S* qt = q + (int64_t)t * q_t;
-    int32_t k = 0;
-    for (; k + 4 <= deg; k += 4) {
-      const int32_t slot = s0 + 64 * k;   // entries k, k+1; k+2, k+3 one pair further
-      const int2 p01 = *reinterpret_cast<const int2*>(pt.sr_col + slot);
-      const int2 p23 = *reinterpret_cast<const int2*>(pt.sr_col + slot + 128);
-      S w0, w1, w2, w3;
-      Load2<ST>::get(v.W, base + slot, v.scale, sbase + (p01.x >> 6), sbase + (p01.y >> 6), w0, w1);
-      Load2<ST>::get(v.W, base + slot + 128, v.scale, sbase + (p23.x >> 6), sbase + (p23.y >> 6), w2,
-                     w3);
-      const S x0 = qt[col_at(p01.x, q_b)], x1 = qt[col_at(p01.y, q_b)];
-      const S x2 = qt[col_at(p23.x, q_b)], x3 = qt[col_at(p23.y, q_b)];
-      acc += w0 * x0;
-      acc += w1 * x1;
-      acc += w2 * x2;
-      acc += w3 * x3;
-    }
-    if (k + 2 <= deg) {
-      const int32_t slot = s0 + 64 * k;
-      const int2 p01 = *reinterpret_cast<const int2*>(pt.sr_col + slot);
-      S w0, w1;
-      Load2<ST>::get(v.W, base + slot, v.scale, sbase + (p01.x >> 6), sbase + (p01.y >> 6), w0, w1);
-      const S x0 = qt[col_at(p01.x, q_b)], x1 = qt[col_at(p01.y, q_b)];
-      acc += w0 * x0;
-      acc += w1 * x1;
-      k += 2;
-    }
-    if (k < deg) {
-      const int32_t slot = s0 + 64 * k;
-      const int p = pt.sr_col[slot];
-      acc += static_cast<S>(Load<ST>::get(v.W, base + slot, v.scale, sbase + (p >> 6))) *
-             qt[col_at(p, q_b)];
-    }
-  }
-  return acc;
-}
-
-// Column (t, p) of rho_c^T applied to residual rows: sum over lags l whose row
-// block h = t+l is in the minibatch (slot pos[h]-first in [0, bh)) of sum_{a on p} W[l][t][a,p] r[slot][a].
-// The column's entries are taken in CSC order from the OD-sliced layout, four
-// steps' loads issued together.
-template <int ST, typename S>
-__device__ __forceinline__ S col_dot_chunk(const DevPat& pt, const DevVals& v, int c, int t, int p,
-                                           const int32_t* pos_c, int32_t first, int32_t bh,
-                                           const S* Rd, int64_t r_s, int64_t r_b) {
-  S acc = 0;
-  const int32_t deg = pt.col_ptr[p + 1] - pt.col_ptr[p];
-  const int32_t s0 = pt.sc_off[p >> 6] + (p & 63);
-  for (int l = 0; l < pt.K; ++l) {
-    const int h = t + l;
-    if (h >= pt.H) break;
-    const int s = pos_c ? pos_c[h] - first : h;
-    if (s < 0 || s >= bh) continue;
-    const int64_t base = c * v.cstride_c + ((int64_t)l * pt.T + t) * pt.sc_len;
-    const int64_t si = (c * (int64_t)pt.K * pt.T + (int64_t)l * pt.T + t) * v.n_ptile + (p >> 6);
-    const S* r = Rd + (int64_t)s * r_s;
-    int32_t k = 0;
-    for (; k + 4 <= deg; k += 4) {
-      S w[4], x[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int32_t slot = s0 + 64 * (k + u);
-        w[u] = static_cast<S>(Load<ST>::get(v.WT, base + slot, v.scale, si));
-        x[u] = r[col_at(pt.sc_row[slot], r_b)];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) acc += w[u] * x[u];
-    }
-    for (; k < deg; ++k) {
-      const int32_t slot = s0 + 64 * k;
-      acc += static_cast<S>(Load<ST>::get(v.WT, base + slot, v.scale, si)) * r[col_at(pt.sc_row[slot], r_b)];
-    }
-  }
-  return acc;
 }
 
 // ------------------------------------------------------------- kernels --
@@ -310,22 +138,31 @@ k_adjoint_rows(DevPat pt, DevVals v, const int32_t* day_cluster, int32_t cluster
         col_dot_chunk<ST, S>(pt, v, c, t, p, nullptr, 0, pt.H, Rd, ly.r_s, ly.r_b);
 }
 
-__global__ void k_sum_partials(const double* __restrict__ part, int32_t n_per, int32_t n_days,
-                               double* __restrict__ out) {
-  const int d = blockIdx.x * blockDim.x + threadIdx.x;
+// One wave per day: lane i takes partials i, i+64, ..., then a butterfly (fixed
+// order).  One thread per day left a serial chain of 288 loads: 22 us for any
+// number of days.
+__global__ void __launch_bounds__(kRedBlock)
+k_sum_partials(const double* __restrict__ part, int32_t n_per, int32_t n_days,
+               double* __restrict__ out) {
+  const int d = blockIdx.x * (kRedBlock / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (d >= n_days) return;
   double s = 0.0;
-  for (int i = 0; i < n_per; ++i) s += part[(int64_t)d * n_per + i];
-  out[d] = s;
+  for (int i = lane; i < n_per; i += 64) s += part[(int64_t)d * n_per + i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if (lane == 0) out[d] = s;
 }
 
-__global__ void k_max_partials(const double* __restrict__ part, int32_t n_per, int32_t n_days,
-                               double* __restrict__ out) {
-  const int d = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(kRedBlock)
+k_max_partials(const double* __restrict__ part, int32_t n_per, int32_t n_days,
+               double* __restrict__ out) {
+  const int d = blockIdx.x * (kRedBlock / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (d >= n_days) return;
   double m = 0.0;
-  for (int i = 0; i < n_per; ++i) m = fmax(m, part[(int64_t)d * n_per + i]);
-  out[d] = m;
+  for (int i = lane; i < n_per; i += 64) m = fmax(m, part[(int64_t)d * n_per + i]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+  if (lane == 0) out[d] = m;
 }
 
 template <typename S>
@@ -380,53 +217,6 @@ __global__ void k_clamp(S* __restrict__ Q, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
     Q[i] = Q[i] > S(0) ? Q[i] : S(0);
-}
-
-template <typename S>
-__global__ void __launch_bounds__(kRedBlock)
-k_quantize(DevPat pt, int32_t storage, int32_t c, const S* __restrict__ Wsrc, void* W, void* WT,
-           float* scale, const int32_t* __restrict__ csc2csr, int64_t cstride_r, int64_t cstride_c,
-           int32_t n_ptile) {
-  // one block per (l, t) block of cluster c; the source is in CSR order, the
-  // two copies are written in their sliced layouts
-  const int lt = blockIdx.x;
-  const S* src = Wsrc + (int64_t)lt * pt.nnz;
-  const int64_t dr = c * cstride_r + (int64_t)lt * pt.sr_len;
-  const int64_t dc = c * cstride_c + (int64_t)lt * pt.sc_len;
-  __shared__ float smax[64];
-  if (storage == DODE_FP8_E4M3) {
-    for (int i = threadIdx.x; i < n_ptile; i += blockDim.x) smax[i] = 0.f;
-    __syncthreads();
-    for (int64_t j = threadIdx.x; j < pt.nnz; j += blockDim.x) {
-      const float a = fabsf(static_cast<float>(src[j]));
-      atomicMax(reinterpret_cast<unsigned int*>(&smax[pt.col[j] >> 6]), __float_as_uint(a));
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < n_ptile; i += blockDim.x)
-      scale[((int64_t)c * pt.K * pt.T + lt) * n_ptile + i] = smax[i] > 0.f ? smax[i] / 448.f : 1.f;
-    __syncthreads();
-  }
-  for (int64_t jj = threadIdx.x; jj < pt.nnz; jj += blockDim.x) {
-    const int64_t j = csc2csr[jj];
-    const int64_t oj = dr + pt.sr_pos[j], ojj = dc + pt.sc_pos[jj];
-    const float w = static_cast<float>(src[j]);
-    if (storage == DODE_F32) {
-      static_cast<float*>(W)[oj] = w;
-      static_cast<float*>(WT)[ojj] = w;
-    } else if (storage == DODE_BF16) {
-      const uint16_t b = f32_to_bf16_rne(w);
-      static_cast<uint16_t*>(W)[oj] = b;
-      static_cast<uint16_t*>(WT)[ojj] = b;
-    } else if (storage == DODE_FP8_E4M3) {
-      const float sc = smax[pt.col[j] >> 6] > 0.f ? smax[pt.col[j] >> 6] / 448.f : 1.f;
-      const uint8_t b = f32_to_e4m3_rne(w / sc);
-      static_cast<uint8_t*>(W)[oj] = b;
-      static_cast<uint8_t*>(WT)[ojj] = b;
-    } else {
-      static_cast<double*>(W)[oj] = static_cast<double>(src[j]);
-      static_cast<double*>(WT)[ojj] = static_cast<double>(src[j]);
-    }
-  }
 }
 
 template <template <int, typename> class F, typename... Args>
@@ -616,14 +406,14 @@ hipError_t permute_loss(const double* src, const int32_t* order, int32_t D, doub
 
 hipError_t sum_partials(const double* part, int32_t n_per, int32_t n_days, double* out,
                         hipStream_t s) {
-  hipLaunchKernelGGL(k_sum_partials, dim3((n_days + 127) / 128), dim3(128), 0, s, part, n_per,
+  hipLaunchKernelGGL(k_sum_partials, dim3((n_days + 3) / 4), dim3(kRedBlock), 0, s, part, n_per,
                      n_days, out);
   return hipGetLastError();
 }
 
 hipError_t max_partials(const double* part, int32_t n_per, int32_t n_days, double* out,
                         hipStream_t s) {
-  hipLaunchKernelGGL(k_max_partials, dim3((n_days + 127) / 128), dim3(128), 0, s, part, n_per,
+  hipLaunchKernelGGL(k_max_partials, dim3((n_days + 3) / 4), dim3(kRedBlock), 0, s, part, n_per,
                      n_days, out);
   return hipGetLastError();
 }
@@ -673,22 +463,5 @@ hipError_t clamp_nonneg(bool f64, void* Q, int64_t n, hipStream_t s) {
     hipLaunchKernelGGL(k_clamp<double>, dim3(blocks), dim3(256), 0, s, static_cast<double*>(Q), n);
   else
     hipLaunchKernelGGL(k_clamp<float>, dim3(blocks), dim3(256), 0, s, static_cast<float*>(Q), n);
-  return hipGetLastError();
-}
-
-hipError_t quantize_values(const dode_dar* dar, int32_t cluster, const void* W_state,
-                           hipStream_t s) {
-  const dim3 grid(dar->dims.K * dar->dims.T);
-  const int32_t n_ptile = (dar->dims.P + 63) / 64;
-  if (dar->storage == DODE_F64)
-    hipLaunchKernelGGL(k_quantize<double>, grid, dim3(kRedBlock), 0, s, dar->pat(),
-                       (int32_t)dar->storage, cluster, static_cast<const double*>(W_state), dar->d_W,
-                       dar->d_WT, dar->d_scale, dar->d_csc2csr, dar->vals().cstride_r,
-                       dar->vals().cstride_c, n_ptile);
-  else
-    hipLaunchKernelGGL(k_quantize<float>, grid, dim3(kRedBlock), 0, s, dar->pat(),
-                       (int32_t)dar->storage, cluster, static_cast<const float*>(W_state), dar->d_W,
-                       dar->d_WT, dar->d_scale, dar->d_csc2csr, dar->vals().cstride_r,
-                       dar->vals().cstride_c, n_ptile);
   return hipGetLastError();
 }

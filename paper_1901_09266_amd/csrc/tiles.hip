@@ -115,15 +115,14 @@ dode_status tiles_prepare(dode_dar* d, std::string& err) {
     return hip_ok(hipMemcpy(*dst, v.data(), v.size() * 4, hipMemcpyHostToDevice));
   };
   d->h_tile_meta = meta;
-  if (!up(&d->d_tile_meta, meta) || !up(&d->d_posf, d->h_posf) || !up(&d->d_posg, d->h_posg))
-    return DODE_ERR_OOM;
+  if (!up(&d->d_tile_meta, meta)) return DODE_ERR_OOM;
   const size_t esz = d->storage == DODE_FP8_E4M3 ? 1 : 2;
   const int64_t blocks = (int64_t)dm.K * dm.T;
   const size_t fbytes = (size_t)d->C * blocks * kf * 512 * esz;
   const size_t gbytes = (size_t)d->C * blocks * kg * 512 * esz;
   if (!hip_ok(hipMalloc(&d->d_Fv, std::max<size_t>(16, fbytes)))) return DODE_ERR_OOM;
   if (!hip_ok(hipMalloc(&d->d_Gv, std::max<size_t>(16, gbytes)))) return DODE_ERR_OOM;
-  d->device_bytes += fbytes + gbytes + meta.size() * 4 + 8 * nnz;
+  d->device_bytes += fbytes + gbytes + meta.size() * 4;
   if (d->has_corr) {
     // bf16 correction tiles, 2 bytes per entry whatever the storage type
     const size_t cf = fbytes / esz * 2, cg = gbytes / esz * 2;
@@ -189,12 +188,6 @@ dode_status fill_tiles(dode_dar* d, int32_t c, const E* codes_csr, void* F, void
 }
 
 }  // namespace
-
-dode_status tiles_fill_cluster(dode_dar* d, int32_t c, const void* codes_csr, std::string& err) {
-  if (d->storage == DODE_FP8_E4M3)
-    return fill_tiles(d, c, static_cast<const uint8_t*>(codes_csr), d->d_Fv, d->d_Gv, err);
-  return fill_tiles(d, c, static_cast<const uint16_t*>(codes_csr), d->d_Fv, d->d_Gv, err);
-}
 
 dode_status tiles_fill_correction(dode_dar* d, int32_t c, const uint16_t* corr_csr,
                                   std::string& err) {
