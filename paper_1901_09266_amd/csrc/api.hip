@@ -1506,7 +1506,8 @@ namespace {
 // will use), then the lengths and speeds on the device.
 dode_status check_paths_speeds(int32_t n_paths, const int32_t* path_ptr, const int32_t* path_link,
                                int64_t n_pairs, int32_t L, const void* link_len, const void* speed,
-                               int32_t n_days, int32_t H_speed, bool f64, hipStream_t s) {
+                               int32_t n_days, int32_t H_speed, bool f64, hipStream_t s,
+                               int32_t* longest = nullptr) {
   std::vector<int32_t> hp(n_paths + 1), hl((size_t)n_pairs);
   HIP_TRY(hipMemcpyAsync(hp.data(), path_ptr, hp.size() * 4, hipMemcpyDeviceToHost, s));
   if (n_pairs) HIP_TRY(hipMemcpyAsync(hl.data(), path_link, hl.size() * 4, hipMemcpyDeviceToHost, s));
@@ -1518,6 +1519,10 @@ dode_status check_paths_speeds(int32_t n_paths, const int32_t* path_ptr, const i
   for (int64_t m = 0; m < n_pairs; ++m)
     if (hl[m] < 0 || hl[m] >= L)
       return fail(DODE_ERR_SHAPE, "path_link[%lld]=%d outside [0, L)", (long long)m, hl[m]);
+  if (longest) {
+    *longest = 0;
+    for (int32_t k = 0; k < n_paths; ++k) *longest = std::max(*longest, hp[k + 1] - hp[k]);
+  }
   DevBuf flag;
   HIP_TRY(flag.alloc(4, s));
   HIP_TRY(fill_zero(false, flag.p, 1, s));
@@ -1554,8 +1559,9 @@ dode_status dode_dar_patterns_from_speeds(int32_t n_paths, const int32_t* path_p
     return fail(DODE_ERR_ARG, "path_ptr, path_link, link_len, speed or Rr is NULL");
   hipStream_t s = as_stream(stream);
   // one check of the path tables and of every day's speeds for the whole job
+  int32_t longest = 0;
   if (dode_status st = check_paths_speeds(n_paths, path_ptr, path_link, n_pairs, L, link_len, speed,
-                                          n_days, H_speed, f64 != 0, s))
+                                          n_days, H_speed, f64 != 0, s, &longest))
     return st;
   // trajectory scratch (and path exit times) for a chunk of days, at most
   // 4 GiB or DODE_DAR_SCRATCH_BYTES (at least one day), shared by the patterns
@@ -1568,6 +1574,11 @@ dode_status dode_dar_patterns_from_speeds(int32_t n_paths, const int32_t* path_p
     if (e[0] < '0' || e[0] > '9' || *end != '\0' || v == 0)
       return fail(DODE_ERR_ARG, "DODE_DAR_SCRATCH_BYTES='%s' is not a positive byte count", e);
     limit = (size_t)v;
+  }
+  if (dar_fused(f64 != 0, n_paths, longest, H, H_speed, K, n_patterns)) {   // no scratch
+    HIP_TRY(dar_ratios(f64 != 0, n_paths, path_ptr, path_link, n_pairs, longest, L, link_len, speed,
+                       n_patterns, pattern_ptr, H_speed, dt, H, K, Rr, cost, s));
+    return DODE_OK;
   }
   int32_t most = 0;
   for (int32_t q = 0; q < n_patterns; ++q) most = std::max(most, pattern_ptr[q + 1] - pattern_ptr[q]);

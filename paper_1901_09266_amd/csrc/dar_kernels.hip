@@ -10,7 +10,8 @@
 // arrival window [tau_i(h dt), tau_i((h+1) dt)] at that link, and the ratio of
 // observation interval h2 is the share of the window inside it.
 //
-// Two kernels per chunk of days:
+// Paths of up to 16 segments of links take one kernel (k_ratios below); longer
+// ones two kernels per chunk of days:
 //   k_trajectories  one thread per (eight days, path, boundary b in 0..H): the travel
 //                   time from the b*dt departure to the entry of every link of
 //                   the path, traj[day][pair][b] (pairs = (path, i) in path
@@ -198,6 +199,166 @@ k_dar_windows(int64_t n_pairs, int32_t n_days_chunk, int32_t H, int32_t K, S dt,
   }
 }
 
+// The whole ratio construction of several patterns in one kernel: no
+// trajectory leaves the chip.
+//
+// A block owns one path and 63 departure intervals of one pattern: lane i
+// walks the boundary departure b0 + i, and the window of interval b0 + i needs
+// its own and the next lane's entry times (lane 63 only supplies lane 62).  The
+// path's links are cut into segments of SEG, one per wave, whose shares stay in
+// registers (SEG x KMAX sums per lane) over all days; wave s takes the travel
+// times of ND days from wave s-1 through LDS and passes them on, so the waves
+// form a pipeline over the groups of days, one step per barrier.  The speed
+// gathers of a link are in flight while its windows are added.  Days are added
+// in order, so the results are those of the two kernels above for any grouping.
+//
+// What bounds it: the VALU (about 45 instructions per day, link and boundary
+// in FP32) and the chain of gathers along a path.  The trajectories of the two
+// kernels above (4 bytes per day, link and boundary, written, read twice, and a
+// scratch allocation of up to 4 GiB that the call's own synchronisation
+// gives back each time) took 52 ms for 365 days of 450 paths of 20 links at
+// 288 intervals and 6 lags in 4 patterns, of which 3.6 ms were kernels.
+constexpr int kMaxSegs = 16;   // waves of a block
+constexpr int kPatterns = 16;  // patterns of one launch
+struct PatternDays {
+  int32_t ptr[kPatterns + 1];
+};
+
+// RN(t / dt) with rdt = RN(1 / dt): two residual steps on the approximate
+// quotient, the second of which rounds correctly (Markstein, IBM J. Res. Dev.
+// 34, 1990).  The interval of an entry time is decided by this quotient.
+__device__ __forceinline__ float quotient(float t, float dt, float rdt) {
+  float q = t * rdt;
+  q = __builtin_fmaf(__builtin_fmaf(-q, dt, t), rdt, q);
+  return __builtin_fmaf(__builtin_fmaf(-q, dt, t), rdt, q);
+}
+__device__ __forceinline__ double quotient(double t, double dt, double) { return t / dt; }
+
+// value of the next lane (lane 63 keeps its own)
+__device__ __forceinline__ float next_lane(float x) { return __shfl_down(x, 1, 64); }
+__device__ __forceinline__ double next_lane(double x) { return __shfl_down(x, 1, 64); }
+
+template <typename S, int KMAX, int SEG, int ND>
+__global__ void __launch_bounds__(64 * kMaxSegs)
+k_ratios(int32_t n_paths, const int32_t* __restrict__ path_ptr,
+         const int32_t* __restrict__ path_link, int32_t L, const S* __restrict__ len,
+         const S* __restrict__ speed, PatternDays days, int32_t H_speed, S dt, S rdt, int32_t H,
+         int32_t K, int64_t n_pairs, S* __restrict__ Rr, S* __restrict__ cost) {
+#pragma clang fp contract(off)   // as in k_trajectories
+  constexpr int kWin = 63;
+  extern __shared__ __align__(16) unsigned char hand_mem[];
+  S* hand = reinterpret_cast<S*>(hand_mem);   // [2][waves][ND][64]
+  const int nw = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int n_chunks = (H + kWin - 1) / kWin;
+  int item = blockIdx.x;
+  const int chunk = item % n_chunks;
+  item /= n_chunks;
+  const int k = item % n_paths, q = item / n_paths;
+  const int d_begin = days.ptr[q], n_days = days.ptr[q + 1] - d_begin;
+  const int m0 = path_ptr[k], m_end = path_ptr[k + 1];
+  const int n_segs = max(1, (m_end - m0 + SEG - 1) / SEG);
+  const int m = m0 + wave * SEG;   // first pair of the wave's segment
+  const int n_links = wave < n_segs ? min(SEG, m_end - m) : 0;
+  const int b = min(chunk * kWin + lane, H);
+  const S t0 = static_cast<S>(b) * dt;
+  const int64_t day_stride = (int64_t)L * H_speed;
+  // the segment's links (uniform)
+  int64_t row[SEG];
+  S ln[SEG];
+#pragma unroll
+  for (int i = 0; i < SEG; ++i)
+    if (i < n_links) {
+      const int a = path_link[m + i];
+      row[i] = (int64_t)a * H_speed;
+      ln[i] = len[a];
+    }
+  S edge[KMAX], acc[SEG][KMAX];
+#pragma unroll
+  for (int l = 0; l < KMAX; ++l) {
+    edge[l] = static_cast<S>(l + 1) * dt;
+#pragma unroll
+    for (int i = 0; i < SEG; ++i) acc[i][l] = S(0);
+  }
+  double exit_sum = 0.0;
+  const int n_groups = (n_days + ND - 1) / ND;
+  const S h_last = static_cast<S>(H_speed - 1);
+  for (int st = 0; st < n_groups + n_segs - 1; ++st) {
+    const int g = st - wave;
+    if (wave < n_segs && g >= 0 && g < n_groups) {
+      const int d0 = g * ND, nd = min(ND, n_days - d0);
+      const S* sp = speed + (int64_t)(d_begin + d0) * day_stride;
+      S r[ND];
+#pragma unroll
+      for (int u = 0; u < ND; ++u)
+        r[u] = wave == 0 ? S(0)
+                         : hand[((((st + 1) & 1) * nw + wave - 1) * ND + u) * 64 + lane];
+#pragma unroll
+      for (int i = 0; i < SEG; ++i) {
+        if (i < n_links) {
+          // entry intervals and speeds (days past the pattern repeat its last)
+          S v[ND];
+#pragma unroll
+          for (int u = 0; u < ND; ++u) {
+            const S f = floor(quotient(t0 + r[u], dt, rdt));
+            const int h = static_cast<int>(fmax(fmin(f, h_last), S(0)));
+            v[u] = (sp + (int64_t)min(u, nd - 1) * day_stride + row[i])[(uint32_t)h];
+          }
+          // the link's window shares (as in k_dar_windows)
+#pragma unroll
+          for (int u = 0; u < ND; ++u) {
+            if (u < nd) {
+              const S lo = r[u], hi = dt + next_lane(r[u]);
+              const S a0 = fmin(lo, hi), w = fmax(lo, hi) - a0;
+              if (w <= S(0)) {
+                const int la = static_cast<int>(fmin(floor(a0 / dt), static_cast<S>(KMAX)));
+#pragma unroll
+                for (int l = 0; l < KMAX; ++l)
+                  if (l == la) acc[i][l] += S(1);
+              } else {
+                const S inv_w = share_recip(w);
+                S f_prev = S(0);
+#pragma unroll
+                for (int l = 0; l < KMAX; ++l) {
+                  const S f = clamp01((edge[l] - a0) * inv_w);
+                  acc[i][l] += f - f_prev;
+                  f_prev = f;
+                }
+              }
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < ND; ++u) r[u] += ln[i] / v[u];
+        }
+      }
+      if (wave == n_segs - 1) {
+#pragma unroll
+        for (int u = 0; u < ND; ++u)
+          if (u < nd) exit_sum += static_cast<double>(r[u]);
+      } else {
+#pragma unroll
+        for (int u = 0; u < ND; ++u)
+          hand[(((st & 1) * nw + wave) * ND + u) * 64 + lane] = r[u];
+      }
+    }
+    __syncthreads();
+  }
+  const int h = chunk * kWin + lane;   // the lane's interval
+  if (lane == kWin || h >= H) return;
+  if (cost && wave == n_segs - 1)
+    cost[((int64_t)q * H + h) * n_paths + k] = static_cast<S>(exit_sum / n_days);
+  const int kk = min(K, H - h);   // lags that stay inside the day
+#pragma unroll
+  for (int l = 0; l < KMAX; ++l) {
+    if (l < K) {
+      S* out = Rr + (((int64_t)q * K + l) * H + h) * n_pairs + m;
+#pragma unroll
+      for (int i = 0; i < SEG; ++i)
+        if (i < n_links) out[i] = l >= kk ? S(0) : acc[i][l] / static_cast<S>(n_days);
+    }
+  }
+}
+
 template <typename S>
 __global__ void __launch_bounds__(kBlock)
 k_path_cost_slices(int32_t n_paths, const int32_t* __restrict__ path_ptr,
@@ -290,6 +451,53 @@ hipError_t run(int32_t n_paths, const int32_t* path_ptr, const int32_t* path_lin
   return hipSuccess;
 }
 
+// Links per wave and days in flight of the fused kernel: the sums of a segment
+// take SEG * KMAX registers (two each in FP64).
+template <typename S, int KMAX>
+struct Seg {
+  static constexpr int kLinks = sizeof(S) == 4 ? (KMAX <= 8 ? 8 : 4) : (KMAX <= 8 ? 4 : 2);
+  static constexpr int kDays = sizeof(S) == 4 ? 8 : (KMAX <= 8 ? 4 : 2);
+};
+
+template <typename S, int KMAX>
+hipError_t run_fused(int32_t n_paths, const int32_t* path_ptr, const int32_t* path_link,
+                     int64_t n_pairs, int32_t longest, int32_t L, const S* len, const S* speed,
+                     int32_t n_patterns, const int32_t* pattern_ptr, int32_t H_speed, S dt,
+                     int32_t H, int32_t K, S* Rr, S* cost, hipStream_t s) {
+  constexpr int SEG = Seg<S, KMAX>::kLinks, ND = Seg<S, KMAX>::kDays;
+  const int nw = std::max(1, (longest + SEG - 1) / SEG);
+  const int64_t per = (int64_t)n_paths * ((H + 62) / 63);
+  const size_t lds = (size_t)2 * nw * ND * 64 * sizeof(S);
+  for (int32_t q0 = 0; q0 < n_patterns; q0 += kPatterns) {
+    const int32_t nq = std::min(kPatterns, n_patterns - q0);
+    PatternDays pd{};
+    for (int32_t q = 0; q <= nq; ++q) pd.ptr[q] = pattern_ptr[q0 + q];
+    hipLaunchKernelGGL((k_ratios<S, KMAX, SEG, ND>), dim3((unsigned)(per * nq)), dim3(64 * nw), lds,
+                       s, n_paths, path_ptr, path_link, L, len, speed, pd, H_speed, dt,
+                       static_cast<S>(1) / dt, H, K, n_pairs,
+                       Rr + (int64_t)q0 * K * H * n_pairs,
+                       cost ? cost + (int64_t)q0 * H * n_paths : nullptr);
+  }
+  return hipGetLastError();
+}
+
+template <typename S>
+hipError_t fused(int32_t n_paths, const int32_t* path_ptr, const int32_t* path_link,
+                 int64_t n_pairs, int32_t longest, int32_t L, const void* len, const void* speed,
+                 int32_t n_patterns, const int32_t* pattern_ptr, int32_t H_speed, double dt,
+                 int32_t H, int32_t K, void* Rr, void* cost, hipStream_t s) {
+  auto go = [&](auto kmax) {
+    return run_fused<S, decltype(kmax)::value>(
+        n_paths, path_ptr, path_link, n_pairs, longest, L, static_cast<const S*>(len),
+        static_cast<const S*>(speed), n_patterns, pattern_ptr, H_speed, static_cast<S>(dt), H, K,
+        static_cast<S*>(Rr), static_cast<S*>(cost), s);
+  };
+  if (K <= 3) return go(std::integral_constant<int, 3>{});
+  if (K <= 6) return go(std::integral_constant<int, 6>{});
+  if (K <= 8) return go(std::integral_constant<int, 8>{});
+  return go(std::integral_constant<int, kMaxDarLags>{});
+}
+
 template <typename S>
 hipError_t run_costs(int32_t n_paths, const int32_t* path_ptr, const int32_t* path_link, int32_t L,
                      const S* len, const S* speed, int32_t n_days, int32_t H_speed, S dt, int32_t T,
@@ -344,4 +552,23 @@ hipError_t dar_from_speeds(bool f64, int32_t n_paths, const int32_t* path_ptr,
                     static_cast<const float*>(speed), n_days, H_speed, static_cast<float>(dt), H, K,
                     static_cast<float*>(traj), chunk, static_cast<float*>(Rr),
                     static_cast<float*>(exit_time), sums, static_cast<float*>(cost), s);
+}
+
+bool dar_fused(bool f64, int32_t n_paths, int32_t longest, int32_t H, int32_t H_speed, int32_t K,
+               int32_t n_patterns) {
+  const int seg = f64 ? (K <= 8 ? Seg<double, 8>::kLinks : Seg<double, 16>::kLinks)
+                      : (K <= 8 ? Seg<float, 8>::kLinks : Seg<float, 16>::kLinks);
+  const int64_t blocks = (int64_t)n_paths * ((H + 62) / 63) * std::min(n_patterns, kPatterns);
+  return longest <= seg * kMaxSegs && blocks <= INT32_MAX && H_speed <= (1 << 24);
+}
+
+hipError_t dar_ratios(bool f64, int32_t n_paths, const int32_t* path_ptr, const int32_t* path_link,
+                      int64_t n_pairs, int32_t longest, int32_t L, const void* len,
+                      const void* speed, int32_t n_patterns, const int32_t* pattern_ptr,
+                      int32_t H_speed, double dt, int32_t H, int32_t K, void* Rr, void* cost,
+                      hipStream_t s) {
+  return f64 ? fused<double>(n_paths, path_ptr, path_link, n_pairs, longest, L, len, speed,
+                             n_patterns, pattern_ptr, H_speed, dt, H, K, Rr, cost, s)
+             : fused<float>(n_paths, path_ptr, path_link, n_pairs, longest, L, len, speed,
+                            n_patterns, pattern_ptr, H_speed, dt, H, K, Rr, cost, s);
 }
