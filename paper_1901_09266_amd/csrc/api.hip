@@ -1693,12 +1693,17 @@ dode_status dense_spgd_run(int32_t m, int32_t n, int32_t prec, const void* B, co
   const int32_t rows = std::min(chunk, m);
   const int32_t n_slices = (rows + dense_slice_rows() - 1) / dense_slice_rows();
   if (n_slices > 65535) return fail(DODE_ERR_SHAPE, "chunk=%d too large", chunk);
-  DevBuf r, part, loss;
+  DevBuf r, part, loss, res;
+  // residuals of the loss history: as many epochs as 16 MiB hold, at least one
+  const int32_t loss_epochs = (int32_t)std::max<size_t>(
+      1, std::min<size_t>((size_t)E, (size_t(16) << 20) / ((size_t)m * ss)));
+  if (loss_hist) HIP_TRY(res.alloc((size_t)loss_epochs * m * ss, s));
   HIP_TRY(r.alloc((size_t)m * ss, s));
   HIP_TRY(part.alloc((size_t)n_slices * n * ss, s));
   if (loss_hist) HIP_TRY(loss.alloc((size_t)E * 8, s));
   DenseArgs a{m, n, E, chunk, B, y, q, A, perms, r.p, part.p,
-              loss_hist ? loss.as<double>() : nullptr, StepArgs{eta, eps, optimizer}};
+              loss_hist ? loss.as<double>() : nullptr, res.p, loss_epochs,
+              StepArgs{eta, eps, optimizer}};
   const bool vec = ((uintptr_t)B % 16 == 0) && ((uintptr_t)q % 16 == 0) && ((size_t)n * bs) % 16 == 0;
   HIP_TRY(prec == 2 ? dense_spgd_bf16(a, vec, s) : dense_spgd(a, prec == 1, vec, s));
   if (loss_hist) {

@@ -638,6 +638,8 @@ struct DenseArgs {
   void* r;                // scratch [m]
   void* part;             // scratch [ceil(min(chunk, m) / dense_slice_rows())][n]
   double* loss;           // [E] (device) or nullptr
+  void* res;              // scratch [loss_epochs][m] with a loss: residuals after each epoch
+  int32_t loss_epochs;
   StepArgs st;
 };
 int32_t dense_slice_rows();
