@@ -83,8 +83,9 @@ typedef struct {
                           tiles for BF16 / FP8 when a cluster has more than 2
                           days or refine_steps > 0, a forward and an adjoint
                           launch per minibatch; FP32 and FP64 from 32 days in
-                          clusters of several days on FP32 / FP64 matrix-core
-                          products of the pattern; else the sparse kernels),
+                          clusters of several days, and 2^20 products an
+                          epoch, on FP32 / FP64 matrix-core products of the
+                          pattern; else the sparse kernels),
                           1 = sparse pattern kernels, 2 = matrix-core tiles
                           with one launch per minibatch, one workgroup per
                           independent part of it, 3 = matrix-core tiles with

@@ -20,6 +20,18 @@ namespace {
 
 // clusters of at most this many days use the sparse kernels under kernel_path 0
 constexpr int32_t kSparseDays = 2;
+// From how many products (entries * lags * intervals * days) the kernels of 16
+// days per block run: a whole pass below 2^21 and a minibatch's epoch below 2^20
+// is launches and latency, where one day per block is faster (passes at 0.9 M:
+// 42 against 43 us, at 2.3 M 47 against 46, at 5.2 M 99 against 68; epochs of
+// 0.75 M 79 against 92 us, of 1.0 M 120 against 117).  The minibatches also
+// need 32 days in groups that are half full on average: a launch costs what its
+// blocks do, and a block the same for 1 as for 16 days (50 ODs, 200 links, 288
+// intervals, an epoch: 16 days 160 one day per block against 170, 30 days 219
+// against 174, 100 days 469 against 252; in 4 clusters 167 against 189, 226
+// against 204, 487 against 263).
+constexpr int64_t kMinPassProducts = int64_t(1) << 21;
+constexpr int64_t kMinStepProducts = int64_t(1) << 20;
 constexpr int32_t kMinStepDays = 32;
 // handles with packed union tiles: at most this many clusters and bytes
 constexpr int32_t kUnionClusters = 64;
@@ -95,12 +107,20 @@ dode_status check_days(int32_t n_days) {
   return DODE_OK;
 }
 
-// rho_c Q (- X) of n_days days of one cluster in the caller's layout: 16 days
-// per block on the matrix cores, or, where a row of 16 days is too long to
-// stage, one day per block.
+int64_t products(const dode_dar* dar, int32_t n_days) {
+  return dar->nnz * dar->dims.K * std::min<int64_t>(dar->dims.T * (int64_t)n_days, INT32_MAX);
+}
+
+// Days per block of a whole pass over n_days days: 16 on the matrix cores, or,
+// where a row of 16 days is too long to stage or the pass is small, 1.
+int32_t pass_days(const dode_dar* dar, int32_t n_days) {
+  return products(dar, n_days) < kMinPassProducts ? 1 : days_per_group(dar, n_days);
+}
+
+// rho_c Q (- X) of n_days days of one cluster in the caller's layout
 hipError_t apply_rows(const dode_dar* dar, int32_t cluster, const void* Q, const void* X, void* out,
                       double* part, int32_t n_days, hipStream_t s) {
-  const int32_t nd = days_per_group(dar, n_days);
+  const int32_t nd = pass_days(dar, n_days);
   const Layout ly = day_major(dar->dims);
   if (nd == 1) return plain_apply_rows(dar, nullptr, cluster, ly, Q, X, out, part, n_days, s);
   const DayList dl{nullptr, (n_days + nd - 1) / nd, nd, cluster, n_days};
@@ -110,7 +130,7 @@ hipError_t apply_rows(const dode_dar* dar, int32_t cluster, const void* Q, const
 // G = f * rho_c^T R of full residual rows R, the same way
 hipError_t adjoint_rows(const dode_dar* dar, int32_t cluster, const void* R, void* G, double f,
                         int32_t n_days, hipStream_t s) {
-  const int32_t nd = days_per_group(dar, n_days);
+  const int32_t nd = pass_days(dar, n_days);
   const Layout ly = day_major(dar->dims);
   if (nd == 1) {
     const hipError_t e = plain_adjoint_rows(dar, nullptr, cluster, ly, R, G, n_days, s);
@@ -1119,7 +1139,17 @@ dode_status dar_create_ex(const dode_dims* dims, int32_t n_clusters, const int32
     std::vector<int32_t> sr_col(d->sr_len, 0), sc_row(d->sc_len, 0);
     for (int64_t j = 0; j < nnz; ++j) sr_col[sr_pos[j]] = col_idx[j];
     for (int64_t jj = 0; jj < nnz; ++jj) sc_row[sc_pos[jj]] = d->h_row[jj];
-    HIP_TRY(dev_copy(&d->d_sr_first, sr_first));
+    std::vector<int32_t> lanes((size_t)(dm.L + 63) / 64 * 256, 0);
+    for (size_t i = 0; i < lanes.size(); i += 4) lanes[i] = -1;
+    for (int32_t a = 0; a < dm.L; ++a) {
+      int32_t* ln = &lanes[(size_t)4 * (a / 64 * 64 + (sr_first[a] - sr_off[a / 64]) / 2)];
+      ln[0] = a;
+      ln[1] = row_ptr[a + 1] - row_ptr[a];
+      d->max_row = std::max(d->max_row, ln[1]);
+      ln[2] = sr_first[a];
+    }
+    lanes.insert(lanes.end(), sr_first.begin(), sr_first.end());
+    HIP_TRY(dev_copy(&d->d_sr_first, lanes));
     HIP_TRY(dev_copy(&d->d_sr_col, sr_col));
     HIP_TRY(dev_copy(&d->d_sr_pos, sr_pos));
     HIP_TRY(dev_copy(&d->d_sc_off, sc_off));
@@ -1769,7 +1799,7 @@ dode_status spgd_plan_destroy(dode_plan* plan) {
                   (void*)plan->d_slabs,
                   (void*)plan->d_dc, plan->d_R, (void*)plan->d_part, (void*)plan->d_groups, (void*)plan->d_days,
                   (void*)plan->d_full,
-                  plan->d_X, plan->d_Q, plan->d_A, (void*)plan->d_loss, (void*)plan->d_order})
+                  plan->d_X, plan->d_Q, plan->d_A, (void*)plan->d_order})
     if (p) (void)hipFree(p);
   free_wave_tables(plan);
   for (hipEvent_t e : plan->event_pool) (void)hipEventDestroy(e);
@@ -1868,28 +1898,27 @@ dode_status spgd_plan_create(const dode_dar* dar, const int32_t* day_cluster, in
     return fail(DODE_ERR_UNSUPPORTED,
                 "kernel_path 3 runs the chunked adjoint (adj_order 2) with 16-day waves only");
   // day groups of the pattern kernels (FP32 and FP64 minibatches, loss history)
-  p->days.nd = max_days > kSparseDays ? days_per_group(dar, max_days) : 1;
-  if (p->days.nd > 1) {
+  const int64_t work = products(dar, D);
+  int32_t nd = max_days > kSparseDays && work >= kMinStepProducts ? days_per_group(dar, max_days) : 1;
+  if (nd > 1) {
     std::vector<int32_t> gc, gf, gn;
     for (int32_t c = 0, start = 0; c < C; start += p->cluster_days[c++])
-      for (int32_t f = 0; f < p->cluster_days[c]; f += p->days.nd) {
+      for (int32_t f = 0; f < p->cluster_days[c]; f += nd) {
         gc.push_back(c);
         gf.push_back(start + f);
-        gn.push_back(std::min(p->days.nd, p->cluster_days[c] - f));
+        gn.push_back(std::min(nd, p->cluster_days[c] - f));
       }
     p->days.n = (int32_t)gc.size();
-    gc.insert(gc.end(), gf.begin(), gf.end());
-    gc.insert(gc.end(), gn.begin(), gn.end());
-    HIP_TRY(up(&p->d_days, gc.data(), gc.size() * 4));
-    p->days.tab = p->d_days;
+    p->days.nd = nd;
+    p->step_days = params->kernel_path == 0 && D >= kMinStepDays && 2 * D >= nd * p->days.n;
+    p->loss_days = work >= kMinPassProducts;
+    if (p->step_days || p->loss_days) {
+      gc.insert(gc.end(), gf.begin(), gf.end());
+      gc.insert(gc.end(), gn.begin(), gn.end());
+      HIP_TRY(up(&p->d_days, gc.data(), gc.size() * 4));
+      p->days.tab = p->d_days;
+    }
   }
-  // FP32 and FP64 minibatches by day groups from kMinStepDays days in groups
-  // that are half full on average: a launch costs what its blocks do, and a
-  // block the same for 1 as for 16 days (27 days in 3 clusters: 19.9 us per
-  // minibatch against 17.0 one day per block; 92 days in 4 clusters: 1.6 times
-  // faster, 365 days 4 times)
-  p->step_days = p->days.nd > 1 && params->kernel_path == 0 && D >= kMinStepDays &&
-                 2 * D >= p->days.nd * p->days.n;
   p->use_mfma = dar->has_tiles &&
                 ((params->kernel_path == 0 && (max_days > kSparseDays || params->refine_steps > 0)) ||
                  params->kernel_path >= 2);
@@ -1953,7 +1982,6 @@ dode_status spgd_plan_create(const dode_dar* dar, const int32_t* day_cluster, in
   const int64_t nQ = dm.T * p->ly.q_t + kStatePad;
   HIP_TRY(hipMalloc(&p->d_R, nR * ss));
   HIP_TRY(hipMalloc(&p->d_part, (size_t)D * dm.H * 8));
-  HIP_TRY(hipMalloc(&p->d_loss, (size_t)D * 8));
   HIP_TRY(hipMalloc(&p->d_X, nX * ss));
   HIP_TRY(hipMalloc(&p->d_Q, nQ * ss));
   HIP_TRY(hipMalloc(&p->d_A, nQ * ss));
@@ -2045,13 +2073,12 @@ dode_status spgd_run(dode_plan* plan, int32_t epoch_begin, int32_t n_epochs, dou
       double* out = loss_dev + (size_t)(e - epoch_begin) * D;
       HIP_TRY(timed(plan, 2, s, [&] {
         hipError_t r =
-            plan->days.nd > 1
+            plan->loss_days
                 ? days_rows(dar, plan->days, nullptr, dm.H, plan->ly, plan->d_Q, plan->d_X, nullptr,
                             plan->d_part, s)
                 : plain_apply_rows(dar, plan->d_dc, 0, plan->ly, plan->d_Q, plan->d_X, nullptr,
                                    plan->d_part, D, s);
-        if (r == hipSuccess) r = sum_partials(plan->d_part, dm.H, D, plan->d_loss, s);
-        return r != hipSuccess ? r : permute_loss(plan->d_loss, plan->d_order, D, out, s);
+        return r != hipSuccess ? r : sum_partials(plan->d_part, dm.H, D, out, s, plan->d_order);
       }));
     }
   }

@@ -29,6 +29,7 @@ struct DevPat {
   const int32_t* row;       // [nnz]  link of CSC entry jj
   int64_t sr_len, sc_len;   // values per (l, t) block of W / WT
   const int32_t* sr_first;  // [L]          first slot of each link
+  const int4* sr_lane;      // [64*ceil(L/64)] lane of the W slices: its link (-1: none), degree, first slot
   const int32_t* sr_col;    // [sr_len]     OD of each W slot
   const int32_t* sr_pos;    // [nnz]        W slot of CSR entry j
   const int32_t* sc_off;    // [ceil(P/64)] first slot of each OD slice
@@ -110,7 +111,8 @@ struct dode_dar {
   int32_t* d_row = nullptr;
   int32_t* d_row_of_nz = nullptr; // link of CSR slot j
   int64_t sr_len = 0, sc_len = 0;   // sliced value layouts (see DevPat)
-  int32_t* d_sr_first = nullptr;
+  int32_t max_row = 0;              // most ODs of one link
+  int32_t* d_sr_first = nullptr;   // sr_lane, then sr_first
   int32_t* d_sr_col = nullptr;
   int32_t* d_sr_pos = nullptr;
   int32_t* d_sc_off = nullptr;
@@ -145,7 +147,8 @@ struct dode_dar {
 
   DevPat pat() const {
     return DevPat{dims.P, dims.L, dims.T, dims.H, dims.K, nnz, d_row_ptr, d_col, d_col_ptr, d_row,
-                  sr_len, sc_len, d_sr_first, d_sr_col, d_sr_pos, d_sc_off, d_sc_row};
+                  sr_len, sc_len, d_sr_first + 256 * ((dims.L + 63) / 64),
+                  reinterpret_cast<const int4*>(d_sr_first), d_sr_col, d_sr_pos, d_sc_off, d_sc_row};
   }
   DevVals vals() const {
     return DevVals{d_W, d_WT, d_scale, (int64_t)dims.K * dims.T * sr_len,
@@ -426,12 +429,12 @@ struct dode_plan {
   void* d_X = nullptr;            // [H][D][L] plan copy of the observations
   void* d_Q = nullptr;            // [T][D][P] plan copy of the demand
   void* d_A = nullptr;            // [T][D][P] plan copy of the Adagrad accumulator
-  double* d_loss = nullptr;       // [D] loss of the plan's days (plan order)
   int32_t* d_order = nullptr;     // [D] caller day of plan day i (days grouped by cluster)
   Layout ly{};                    // plan layout of X, Q, A, R
   int32_t* d_days = nullptr;      // DayList table of the pattern kernels (nd > 1)
   DayList days{};
   bool step_days = false;         // minibatches of an FP32 / FP64 plan in day groups
+  bool loss_days = false;         // loss passes in day groups
   int32_t* d_groups = nullptr;    // cluster | first | count | cbase | cgroups (n_groups each)
   int32_t n_groups = 0;
   int32_t day_tile = 32;          // days per group
@@ -593,8 +596,6 @@ hipError_t gather_rows(bool f64, const void* src, void* dst, const int32_t* orde
 hipError_t scatter_rows(bool f64, const void* src, void* dst, const int32_t* order, int32_t D,
                         int32_t rows, int32_t n, int64_t sd, int64_t sr, int64_t sb, hipStream_t s);
 hipError_t fill_zero(bool f64, void* x, int64_t n, hipStream_t s);
-hipError_t permute_loss(const double* src, const int32_t* order, int32_t D, double* dst,
-                        hipStream_t s);
 hipError_t set_counter(int32_t* c, int32_t v, hipStream_t s);
 hipError_t bump_counter(int32_t* c, hipStream_t s);
 
@@ -699,8 +700,9 @@ hipError_t loss_bwd_dW(const dode_dar* dar, const void* R, const void* Q, int32_
 hipError_t scale_state(bool f64, void* x, int64_t n, double f, hipStream_t s);
 
 // ---- small generic kernels (plain_kernels.hip) -------------------------
+// out[d], or out[order[d]], = sum of day d's partials
 hipError_t sum_partials(const double* part, int32_t n_per, int32_t n_days, double* out,
-                        hipStream_t s);
+                        hipStream_t s, const int32_t* order = nullptr);
 hipError_t kkt_partials(bool f64, const void* Q, const void* G, int32_t T, int32_t P,
                         int32_t n_days, double* part, hipStream_t s);
 hipError_t max_partials(const double* part, int32_t n_per, int32_t n_days, double* out,
