@@ -654,12 +654,13 @@ dode_status build_wave_tables(dode_plan* plan, const std::vector<std::vector<int
   free_wave_tables(plan);
   const dode_dar* dar = plan->dar;
   if (!dar->has_tiles) return DODE_OK;
+  const int32_t blk = mfma_fwd_shares(dar, plan->day_tile, false) ? kFwdWaves : 1;
   for (size_t k = 0; k < slab_gc.size(); ++k) {
     dode_plan::WaveTables t;
     // the chunked adjoint by chunk, then OD tile, with the day groups fastest
     // (measured fastest: neighbouring waves share the up to kChunkT
     // intervals' tiles, and the OD tiles of a chunk its residual rows)
-    const auto f = work_table(dar, slab_gc[k], slab_gf[k], slab_gn[k], true, plan->bh, false, false);
+    const auto f = work_table(dar, slab_gc[k], slab_gf[k], slab_gn[k], true, plan->bh, false, false, blk);
     const auto a0 = work_table(dar, slab_gc[k], slab_gf[k], slab_gn[k], false, plan->mt, false, false);
     const auto a1 = work_table(dar, slab_gc[k], slab_gf[k], slab_gn[k], false, plan->kmt, true, false);
     const auto a2 = work_table(dar, slab_gc[k], slab_gf[k], slab_gn[k], false, plan->max_chunks,
@@ -675,7 +676,8 @@ dode_status build_wave_tables(dode_plan* plan, const std::vector<std::vector<int
     const int32_t H = dar->dims.H, T = dar->dims.T;
     // full-batch steps: the day groups fastest, so the groups of a cluster
     // read each tile while it is in L2 (the tiles of every interval do not fit)
-    const auto f = work_table(dar, plan->h_gc, plan->h_gf, plan->h_gn, true, H, false, true);
+    const auto f = work_table(dar, plan->h_gc, plan->h_gf, plan->h_gn, true, H, false, true,
+                              mfma_fwd_shares(dar, plan->day_tile, true) ? kFwdWaves : 1);
     const auto a = work_table(dar, plan->h_gc, plan->h_gf, plan->h_gn, false, T, false, true);
     const auto a2 = work_table(dar, plan->h_gc, plan->h_gf, plan->h_gn, false,
                                std::max<int32_t>(1, plan->full_chunks), false, true);

@@ -58,6 +58,11 @@ struct DevVals {
 // (the range covering all of them): one wave multiplies the group's tiles
 // with the same demand operand.
 constexpr int32_t kFwdTileGroup = 2;
+// Forward groups of one block: neighbouring groups of one slot and day group,
+// which share the block's copy of the demand (k_fwd_block).
+constexpr int32_t kFwdWaves = 4;
+constexpr int32_t kFwdStage = 28672;   // LDS of the lags of one phase, where more than one fits
+constexpr int32_t kFwdLds = 65536;     // most LDS of one lag
 
 // Dense MFMA tiles of the assignment blocks (BF16 / FP8 storage).
 //   forward:  link tile i (16 links) x OD hull [f_plo[i], f_plo[i] + 32*f_ks[i])
@@ -135,6 +140,7 @@ struct dode_dar {
   DevTiles tiles;
   int32_t* d_tile_meta = nullptr;   // f_plo | f_ks | f_koff | g_alo | g_ks | g_koff
   std::vector<int32_t> h_tile_meta; // host copy
+  int32_t fwd_span = 0;             // most ODs the tiles of one forward block reach
   // W slot of every WT slot, packed union value and tile element of a block,
   // in the order WT, PR, PC, Fv, Gv (-1: padding)
   int32_t* d_code_of = nullptr;
@@ -350,7 +356,8 @@ struct WaveWork {
 // Work table of one grouped launch over a day-group list (work_tables.hip).
 std::vector<WaveWork> work_table(const dode_dar* dar, const std::vector<int32_t>& gc,
                                  const std::vector<int32_t>& gf, const std::vector<int32_t>& gn,
-                                 bool fwd, int32_t rows, bool tile_major, bool group_fastest);
+                                 bool fwd, int32_t rows, bool tile_major, bool group_fastest,
+                                 int32_t block = 1);
 
 // Day groups of the pattern kernels (days_kernels.hip): groups of up to nd
 // consecutive days of one cluster, from a table (cluster | first | count, n
@@ -652,6 +659,13 @@ hipError_t dense_spgd_bf16(const DenseArgs& a, bool vec, hipStream_t s);
 // ---- MFMA tile kernels (mfma_kernels.hip) -------------------------------
 // corr: multiply with the corrected FP8 values (refinement steps)
 // wt: the launch's work table (n_items entries, one per wave)
+// True where the forward product of `day_tile` days per wave shares the demand
+// in a block (k_fwd_block; its work table comes in blocks of kFwdWaves entries):
+// one lag of the ODs a block reaches fits kFwdLds.  The corrected FP8 values of
+// refinement steps take it with 16 days per wave only: with 32 their operands
+// leave too few registers (205 against 172 us per full pass of 240 days, 400 ODs,
+// 1500 links; with 16 days 200 against 246).
+bool mfma_fwd_shares(const dode_dar* dar, int32_t day_tile, bool corr);
 hipError_t mfma_chunk_resid(const dode_dar* dar, const ChunkSched& cs, const WaveWork* wt,
                             int64_t n_items, int32_t day_tile, const Layout& ly, const float* Q,
                             const float* X, float* R, bool corr, hipStream_t s);

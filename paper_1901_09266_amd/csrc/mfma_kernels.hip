@@ -22,6 +22,9 @@
 // r, col k) at d*4 + r*row_stride + (k/4)*4D + k%4 (strides in Layout).
 #include "dode_internal.h"
 
+#include <algorithm>
+#include <climits>
+
 // No fused multiply-add contraction in this file: the FP8 scale product feeds
 // the hi/lo split, and a contraction chosen differently per template
 // instantiation would make the result depend on the day tile.
@@ -32,9 +35,14 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 // four floats at a 4-byte-aligned address (one global_load_dwordx4 on gfx950)
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
+constexpr int kFwdBlock = 64 * kFwdWaves;
+constexpr int kStageAhead = 8;   // demand loads in flight per thread
+constexpr int kTilesAhead = 3;   // k-steps of assignment values in flight per wave
 constexpr int kXcds = 8;   // gfx950: workgroups are dealt to 8 XCDs round-robin
 
 // Logical block of physical block b: each XCD gets one contiguous range of
@@ -74,7 +82,6 @@ __device__ __forceinline__ f32x4 load4(const float* __restrict__ p) {
 //             bf16 correction tiles; the other operand is not scaled.
 enum { kBF16 = 0, kFP8 = 1, kFP8Corr = 2 };
 
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ f32x8 fp8_codes(const void* tiles, int64_t kidx, int lane) {
   const uint2 w = static_cast<const uint2*>(tiles)[kidx * 64 + lane];
@@ -356,6 +363,7 @@ __device__ __forceinline__ WaveWork load_work(const WaveWork* __restrict__ wt, i
 // Forward product and residual of the minibatch rows, one wave per entry of
 // the launch's work table (slot, day group, link-tile group of a cluster), 4
 // per block; blocks remapped so each XCD walks a contiguous range of the table.
+// For what k_fwd_block does not take (mfma_fwd_shares).
 template <int MODE, int NT>
 __global__ void __launch_bounds__(256)
 k_fwd_mfma(DevPat pt, DevTiles tl, ChunkSched cs, const WaveWork* __restrict__ wt, int n_items,
@@ -370,6 +378,233 @@ k_fwd_mfma(DevPat pt, DevTiles tl, ChunkSched cs, const WaveWork* __restrict__ w
   cs = resolve_epoch(cs);
   const int h = cs.perm[w.c * pt.H + cs.j0 + w.row];
   fwd_group<MODE, NT, kFwdTileGroup>(pt, tl, ly, w, h, Q, X, R);
+}
+
+// Lags [lb, lb + nl) of the demand rows of interval h, ODs [ulo, ulo + 4*nb), as
+// bfloat16 heads and tails in LDS: entry (lag, block of four ODs, day) at 8
+// bytes of either plane, the day group's 16*NT days running fastest.
+template <int MODE, int NT>
+__device__ __forceinline__ void stage_demand(const DevPat& pt, const DevTiles& tl, const Layout& ly,
+                                             int c, int first, int cnt, int h, int lb, int nl,
+                                             int ulo, int nb, const float* __restrict__ Q,
+                                             bf16x4* __restrict__ hi, bf16x4* __restrict__ lo) {
+  constexpr int U = kStageAhead;
+  constexpr int kDays = 16 * NT;
+  const int total = nl * nb * kDays;
+  const unsigned inv = 0xffffffffu / (unsigned)nb + 1;   // x / nb for x * nb < 2^32 (nb > 1)
+  for (int e0 = threadIdx.x; e0 < total; e0 += kFwdBlock * U) {
+    f32x4 v[U];
+    float sc[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = min(e0 + u * kFwdBlock, total - 1);
+      const int day = e & (kDays - 1), r = e / kDays;
+      const int l = nb > 1 ? (int)__umulhi((unsigned)r, inv) : r, b = r - l * nb;
+      const int t = h - lb - l;
+      const int64_t d = day < cnt ? first + day : first;
+      v[u] = load4(Q + d * ly.q_d + t * ly.q_t + ((ulo >> 2) + b) * ly.q_b);
+      if constexpr (MODE == kFP8)
+        sc[u] = tl.scale[(((int64_t)c * pt.K + lb + l) * pt.T + t) * tl.n_ptile +
+                         min((ulo + 4 * b) >> 6, tl.n_ptile - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = e0 + u * kFwdBlock;
+      if (e >= total) break;
+      if constexpr (MODE == kFP8) v[u] *= sc[u];
+      const bf16x4 head = __builtin_convertvector(v[u], bf16x4);
+      hi[e] = head;
+      lo[e] = __builtin_convertvector(v[u] - __builtin_convertvector(head, f32x4), bf16x4);
+    }
+  }
+}
+
+// Assignment operand of one k-step as it is loaded (the FP8 codes still packed).
+template <int MODE>
+struct RawA {
+  bf16x8 a;
+};
+template <>
+struct RawA<kFP8> {
+  uint2 a;
+};
+template <>
+struct RawA<kFP8Corr> {
+  uint2 a;
+  bf16x8 corr;
+};
+
+__device__ __forceinline__ f32x8 widen_codes(const uint2 w) {
+  const f32x2 a = __builtin_amdgcn_cvt_pk_f32_fp8((int)w.x, false);
+  const f32x2 b = __builtin_amdgcn_cvt_pk_f32_fp8((int)w.x, true);
+  const f32x2 c = __builtin_amdgcn_cvt_pk_f32_fp8((int)w.y, false);
+  const f32x2 d = __builtin_amdgcn_cvt_pk_f32_fp8((int)w.y, true);
+  return f32x8{a[0], a[1], b[0], b[1], c[0], c[1], d[0], d[1]};
+}
+
+template <int MODE>
+__device__ __forceinline__ RawA<MODE> load_raw(const DevTiles& tl, int64_t kidx, int lane) {
+  if constexpr (MODE == kBF16)
+    return {static_cast<const bf16x8*>(tl.Fv)[kidx * 64 + lane]};
+  else if constexpr (MODE == kFP8)
+    return {static_cast<const uint2*>(tl.Fv)[kidx * 64 + lane]};
+  else
+    return {static_cast<const uint2*>(tl.Fv)[kidx * 64 + lane], load_corr(tl.Fc, kidx, lane)};
+}
+
+// Forward product and residual of the minibatch rows, the demand shared by a
+// block: kFwdWaves neighbouring link-tile groups of one slot and day group.  The
+// groups of a block reach much the same ODs, and each wave alone loaded them and
+// split them into head and tail for its own one or two k-steps per lag (825 MB
+// through the L1s per launch where the demand is 54).  The block now splits the
+// ODs its groups reach once per lag, in phases of as many lags as kFwdStage
+// holds; the first k-steps' tiles and the observations are on their way
+// meanwhile.  Per tile the products come in increasing lag and k-step order, as
+// in fwd_item.  It is bound by latency with 11 waves per CU on average, not by
+// memory (2 TB/s) or the matrix cores (8%): 1095 days in 8 clusters, 150 ODs, 500
+// links, 16 intervals of 6 lags, bf16, 32 days per wave 58.8 -> 49.8 us; 240 days,
+// 400 ODs, 1500 links, 5 intervals of 3 lags, FP8 17.2 -> 13.8 us.  28 KB of lags
+// was best (40 KB 51.9, 56 KB 56.9: fewer blocks per CU), as were eight demand
+// loads and three k-steps ahead (six: 53.1).
+template <int MODE, int NT>
+__global__ void __launch_bounds__(kFwdBlock)
+k_fwd_block(DevPat pt, DevTiles tl, ChunkSched cs, const WaveWork* __restrict__ wt, int n_items,
+            Layout ly, int lags, const float* __restrict__ Q, const float* __restrict__ X,
+            float* __restrict__ R) {
+  constexpr int TP = kFwdTileGroup, PF = kTilesAhead, kDays = 16 * NT;
+  extern __shared__ char lds[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int blk = xcd_logical_block(n_items / kFwdWaves);
+  if (blk * kFwdWaves >= n_items) return;
+  const WaveWork w = load_work(wt, blk * kFwdWaves + wave);
+  if (cs.j0 + w.row >= pt.H) return;   // one row per block
+  cs = resolve_epoch(cs);
+  const int h = cs.perm[w.c * pt.H + cs.j0 + w.row];
+  int ulo = INT_MAX, uhi = 0;          // ODs the block's tiles reach
+#pragma unroll
+  for (int k = 0; k < kFwdWaves; ++k) {
+    const WaveWork o = load_work(wt, blk * kFwdWaves + k);
+    if (o.nks == 0) continue;
+    ulo = min(ulo, o.lo);
+    uhi = max(uhi, o.lo + 32 * o.nks);
+  }
+  const int nb = max(0, uhi - ulo) / 4;
+  const int lane = threadIdx.x & 63;
+  const int n = lane & 15, kg = lane >> 4;
+  const int i0 = w.tile, nks = w.nks;
+  const int n_tt = min(TP, tl.nLT - i0);   // tiles of this wave (< 1: none, it only stages)
+  const int l_lo = h - pt.T + 1 > 0 ? h - pt.T + 1 : 0;
+  const int l_hi = h < pt.K - 1 ? h : pt.K - 1;
+  const int64_t kbase = (int64_t)w.c * pt.K * pt.T * tl.kf_total + w.koff;
+  f32x4 acc[TP][NT];
+#pragma unroll
+  for (int tt = 0; tt < TP; ++tt)
+#pragma unroll
+    for (int u = 0; u < NT; ++u) acc[tt][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // the observations arrive with the operands (zero blocks end every row, so
+  // the loads past the last link are in bounds)
+  f32x4 x[TP][NT];
+#pragma unroll
+  for (int tt = 0; tt < TP; ++tt)
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+      const int64_t du = 16 * u + n < w.count ? w.first + 16 * u + n : w.first;
+      const int a0 = 16 * (i0 + (tt < n_tt ? tt : 0)) + 4 * kg;
+      x[tt][u] = n_tt < 1 ? f32x4{0.f, 0.f, 0.f, 0.f}
+                          : load4(X + du * ly.x_d + h * ly.x_h + (a0 >> 2) * ly.x_b);
+    }
+  for (int lb = l_lo; lb <= l_hi && nb > 0; lb += lags) {
+    const int nl = min(lags, l_hi + 1 - lb);
+    bf16x4* hi = reinterpret_cast<bf16x4*>(lds);
+    bf16x4* lo = hi + nl * nb * kDays;
+    const int n_it = nl * nks;
+    RawA<MODE> a[PF][TP];
+    float s0[PF], s1[PF];
+    // the loads of iteration (pl, pks), then the next one's indices; past the
+    // last iteration its loads again, with no product
+    int pl = 0, pks = 0;
+    auto fetch = [&](int b) {
+      const int l = lb + pl, t = h - l;
+      const int64_t kidx = kbase + ((int64_t)l * pt.T + t) * tl.kf_total + pks;
+#pragma unroll
+      for (int tt = 0; tt < TP; ++tt)
+        a[b][tt] = load_raw<MODE>(tl, kidx + (tt < n_tt ? tt * nks : 0), lane);
+      if constexpr (MODE == kFP8Corr) {
+        const float* scl = tl.scale + (((int64_t)w.c * pt.K + l) * pt.T + t) * tl.n_ptile;
+        const int p0 = w.lo + 32 * pks + 4 * kg;
+        s0[b] = scl[min(p0 >> 6, tl.n_ptile - 1)];
+        s1[b] = scl[min((p0 + 16) >> 6, tl.n_ptile - 1)];
+      }
+      if (pl * nks + pks + 1 < n_it && ++pks == nks) {
+        pks = 0;
+        ++pl;
+      }
+    };
+    if (n_it > 0) {
+#pragma unroll
+      for (int b = 0; b < PF; ++b) fetch(b);
+    }
+    if (lb > l_lo) __syncthreads();
+    stage_demand<MODE, NT>(pt, tl, ly, w.c, w.first, w.count, h, lb, nl, ulo, nb, Q, hi, lo);
+    __syncthreads();
+    int cl = 0, cks = 0;
+    const int off = ((w.lo - ulo) / 4 + kg) * kDays + n;
+    for (int it0 = 0; it0 < n_it; it0 += PF) {
+#pragma unroll
+      for (int b = 0; b < PF; ++b) {
+        if (it0 + b >= n_it) break;
+        bf16x8 av[TP], cv[MODE == kFP8Corr ? TP : 1];
+#pragma unroll
+        for (int tt = 0; tt < TP; ++tt) {
+          if constexpr (MODE == kBF16) {
+            av[tt] = a[b][tt].a;
+          } else if constexpr (MODE == kFP8) {
+            av[tt] = __builtin_convertvector(widen_codes(a[b][tt].a), bf16x8);
+          } else {
+            f32x8 v = widen_codes(a[b][tt].a);
+            v[0] *= s0[b]; v[1] *= s0[b]; v[2] *= s0[b]; v[3] *= s0[b];
+            v[4] *= s1[b]; v[5] *= s1[b]; v[6] *= s1[b]; v[7] *= s1[b];
+            av[tt] = __builtin_convertvector(v, bf16x8);
+            cv[tt] = a[b][tt].corr;
+          }
+        }
+        const int at = off + (cl * nb + 8 * cks) * kDays;
+#pragma unroll
+        for (int u = 0; u < NT; ++u) {
+          const int e = at + 16 * u;
+          const bf16x8 vh = __builtin_shufflevector(hi[e], hi[e + 4 * kDays], 0, 1, 2, 3, 4, 5, 6, 7);
+          const bf16x8 vl = __builtin_shufflevector(lo[e], lo[e + 4 * kDays], 0, 1, 2, 3, 4, 5, 6, 7);
+#pragma unroll
+          for (int tt = 0; tt < TP; ++tt) {
+            acc[tt][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[tt], vh, acc[tt][u], 0, 0, 0);
+            acc[tt][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[tt], vl, acc[tt][u], 0, 0, 0);
+            if constexpr (MODE == kFP8Corr) {
+              acc[tt][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cv[tt], vh, acc[tt][u], 0, 0, 0);
+              acc[tt][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cv[tt], vl, acc[tt][u], 0, 0, 0);
+            }
+          }
+        }
+        fetch(b);
+        if (++cks == nks) {
+          cks = 0;
+          ++cl;
+        }
+      }
+    }
+  }
+  if (n_tt < 1) return;
+#pragma unroll
+  for (int u = 0; u < NT; ++u) {
+    if (16 * u + n >= w.count) continue;
+    const int64_t du = w.first + 16 * u + n;
+#pragma unroll
+    for (int tt = 0; tt < TP; ++tt) {
+      const int a0 = 16 * (i0 + tt) + 4 * kg;
+      if (tt >= n_tt || a0 >= pt.L) continue;
+      store4(R + du * ly.r_d + w.row * ly.r_s + (a0 >> 2) * ly.r_b, acc[tt][u] - x[tt][u],
+             a0 + 4 <= pt.L, pt.L - a0);
+    }
+  }
 }
 
 __device__ __forceinline__ f32x4 step4(f32x4 q, f32x4& a, const f32x4& g, const StepArgs& st) {
@@ -521,6 +756,7 @@ __device__ __forceinline__ void adj_chunk_item(const DevPat& pt, const DevTiles&
                                                const StepArgs& st) {
   constexpr int CB = NT == 1 ? 1 : 2;   // 4 and 3 waves per SIMD
   constexpr int G = kChunkT;
+  constexpr int kStepRows = 2;   // 1: 67.6, 2: 66.4, 3: 66.8, 6: 68.6 us (1095 days, 150 ODs, 16 intervals)
   const int lane = threadIdx.x & 63;
   const int32_t* cr = ck.chunk + ((int64_t)w.c * ck.max_chunks + w.row) * ck.w;
   const int t0 = cr[0], n_t = cr[1], n_h = cr[2];
@@ -611,25 +847,34 @@ __device__ __forceinline__ void adj_chunk_item(const DevPat& pt, const DevTiles&
   const bool full = p0 + 4 <= pt.P;
   const int valid = pt.P - p0;
   const bool adagrad = st.optimizer == 0;
+  // the rows of kStepRows intervals are fetched together (past the chunk's last
+  // interval its row again): one memory round trip instead of one per interval
 #pragma unroll
-  for (int k = 0; k < G; ++k) {
-    if (k >= n_t) break;
-    const int t = t0 + k;
-    f32x4 q[NT], a[NT];
+  for (int k0 = 0; k0 < G; k0 += kStepRows) {
+    if (k0 >= n_t) break;
+    f32x4 q[kStepRows][NT], a[kStepRows][NT];
 #pragma unroll
-    for (int u = 0; u < NT; ++u) {
-      const int64_t du = live[u] ? first + 16 * u + n : first;
-      const int64_t idx = du * ly.q_d + t * ly.q_t + (p0 >> 2) * ly.q_b;
-      q[u] = load4(Q + idx);
-      a[u] = adagrad ? load4(A + idx) : f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int k = 0; k < kStepRows; ++k)
 #pragma unroll
-    for (int u = 0; u < NT; ++u) {
-      if (!live[u]) continue;
-      const int64_t idx = (int64_t)(first + 16 * u + n) * ly.q_d + t * ly.q_t + (p0 >> 2) * ly.q_b;
-      q[u] = step4(q[u], a[u], acc[k][u], st);
-      store4(Q + idx, q[u], full, valid);
-      if (adagrad) store4(A + idx, a[u], full, valid);
+      for (int u = 0; u < NT; ++u) {
+        const int t = t0 + min(k0 + k, n_t - 1);
+        const int64_t du = live[u] ? first + 16 * u + n : first;
+        const int64_t idx = du * ly.q_d + t * ly.q_t + (p0 >> 2) * ly.q_b;
+        q[k][u] = load4(Q + idx);
+        a[k][u] = adagrad ? load4(A + idx) : f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+    for (int k = 0; k < kStepRows; ++k) {
+      if (k0 + k >= n_t) continue;
+      const int t = t0 + k0 + k;
+#pragma unroll
+      for (int u = 0; u < NT; ++u) {
+        if (!live[u]) continue;
+        const int64_t idx = (int64_t)(first + 16 * u + n) * ly.q_d + t * ly.q_t + (p0 >> 2) * ly.q_b;
+        q[k][u] = step4(q[k][u], a[k][u], acc[k0 + k][u], st);
+        store4(Q + idx, q[k][u], full, valid);
+        if (adagrad) store4(A + idx, a[k][u], full, valid);
+      }
     }
   }
 }
@@ -806,9 +1051,28 @@ k_epoch_persistent(DevPat pt, DevTiles tl, const PersistMinibatch* __restrict__ 
 
 }  // namespace
 
+// LDS of one lag of a forward block's demand
+static int64_t fwd_lag_bytes(const dode_dar* dar, int32_t day_tile) {
+  return (int64_t)dar->fwd_span * day_tile * 4;
+}
+
+bool mfma_fwd_shares(const dode_dar* dar, int32_t day_tile, bool corr) {
+  const int64_t b = fwd_lag_bytes(dar, day_tile);
+  return b > 0 && b <= kFwdLds && !(corr && day_tile > 16);
+}
+
 template <int MODE, int NT>
 hipError_t launch_fwd(const dode_dar* dar, const ChunkSched& cs, const WaveWork* wt, int64_t n,
                       const Layout& ly, const float* Q, const float* X, float* R, hipStream_t s) {
+  if (mfma_fwd_shares(dar, 16 * NT, MODE == kFP8Corr)) {
+    const int64_t lag_bytes = fwd_lag_bytes(dar, 16 * NT);
+    const int lags = (int)std::max<int64_t>(1, std::min<int64_t>(dar->dims.K, kFwdStage / lag_bytes));
+    const int64_t nblk = n / kFwdWaves;
+    const dim3 grid((unsigned)(((nblk + kXcds - 1) / kXcds) * kXcds));
+    hipLaunchKernelGGL((k_fwd_block<MODE, NT>), grid, dim3(kFwdBlock), lags * lag_bytes, s,
+                       dar->pat(), dar->tiles, cs, wt, (int)n, ly, lags, Q, X, R);
+    return hipGetLastError();
+  }
   const int64_t nblk = (n + 3) / 4;
   const dim3 grid((unsigned)(((nblk + kXcds - 1) / kXcds) * kXcds));
   hipLaunchKernelGGL((k_fwd_mfma<MODE, NT>), grid, dim3(256), 0, s, dar->pat(), dar->tiles, cs, wt,

@@ -115,6 +115,15 @@ dode_status tiles_prepare(dode_dar* d, std::string& err) {
     return hip_ok(hipMemcpy(*dst, v.data(), v.size() * 4, hipMemcpyHostToDevice));
   };
   d->h_tile_meta = meta;
+  for (int32_t i = 0; i < nLT; i += kFwdTileGroup * kFwdWaves) {
+    int32_t lo = dm.P, hi = 0;
+    for (int32_t k = i; k < std::min(nLT, i + kFwdTileGroup * kFwdWaves); ++k)
+      if (fh[k].ks > 0) {
+        lo = std::min(lo, fh[k].lo);
+        hi = std::max(hi, fh[k].lo + 32 * fh[k].ks);
+      }
+    d->fwd_span = std::max(d->fwd_span, hi - lo);
+  }
   if (!up(&d->d_tile_meta, meta)) return DODE_ERR_OOM;
   const size_t esz = d->storage == DODE_FP8_E4M3 ? 1 : 2;
   const int64_t blocks = (int64_t)dm.K * dm.T;

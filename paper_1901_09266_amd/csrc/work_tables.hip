@@ -16,9 +16,12 @@
 // (and the same rows of the tiles) for different days.  fwd: rows are
 // minibatch slots, tiles link tiles (kFwdTileGroup per wave, tile = the
 // first); adjoint: rows are descriptor or chunk indices, tiles OD tiles.
+// `block` tiles of one row and group stay together as one unit of that order
+// (past the last tile: entries without k-steps).
 std::vector<WaveWork> work_table(const dode_dar* dar, const std::vector<int32_t>& gc,
                                  const std::vector<int32_t>& gf, const std::vector<int32_t>& gn,
-                                 bool fwd, int32_t rows, bool tile_major, bool group_fastest) {
+                                 bool fwd, int32_t rows, bool tile_major, bool group_fastest,
+                                 int32_t block) {
   const int32_t nLT = dar->tiles.nLT, nPT = dar->tiles.nPT;
   const std::vector<int32_t>& m = dar->h_tile_meta;
   const int32_t* ks = fwd ? m.data() + nLT : m.data() + 3 * nLT + nPT;
@@ -26,12 +29,18 @@ std::vector<WaveWork> work_table(const dode_dar* dar, const std::vector<int32_t>
   const int32_t* ko = fwd ? m.data() + 2 * nLT : m.data() + 3 * nLT + 2 * nPT;
   const int32_t step = fwd ? kFwdTileGroup : 1;
   const int32_t n_tiles = fwd ? (nLT + step - 1) / step : nPT;
-  const int32_t per = tile_major ? n_tiles : rows, inner = tile_major ? rows : n_tiles;
+  const int32_t n_blocks = (n_tiles + block - 1) / block;
+  const int32_t per = tile_major ? n_tiles : rows, inner = tile_major ? rows : n_blocks;
   std::vector<WaveWork> out;
-  out.reserve((size_t)gc.size() * rows * n_tiles);
+  out.reserve((size_t)gc.size() * rows * n_blocks * block);
   auto push = [&](int32_t a, int32_t b, size_t g, size_t g0) {
-    const int32_t row = tile_major ? b : a, tile = (tile_major ? a : b) * step;
-    out.push_back(WaveWork{gc[g0], gf[g], gn[g], row, tile, ks[tile], lo[tile], ko[tile]});
+    const int32_t row = tile_major ? b : a;
+    for (int32_t k = 0; k < block; ++k) {
+      const int32_t tile = ((tile_major ? a : b) * block + k) * step;
+      const bool in = tile < (fwd ? nLT : nPT);
+      out.push_back(WaveWork{gc[g0], gf[g], gn[g], row, in ? tile : nLT, in ? ks[tile] : 0,
+                             in ? lo[tile] : 0, in ? ko[tile] : 0});
+    }
   };
   for (size_t g0 = 0; g0 < gc.size();) {
     size_t g1 = g0 + 1;
