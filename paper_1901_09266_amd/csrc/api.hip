@@ -21,16 +21,16 @@ namespace {
 // clusters of at most this many days use the sparse kernels under kernel_path 0
 constexpr int32_t kSparseDays = 2;
 // From how many products (entries * lags * intervals * days) the kernels of 16
-// days per block run: a whole pass below 2^21 and a minibatch's epoch below 2^20
-// is launches and latency, where one day per block is faster (passes at 0.9 M:
-// 42 against 43 us, at 2.3 M 47 against 46, at 5.2 M 99 against 68; epochs of
-// 0.75 M 79 against 92 us, of 1.0 M 120 against 117).  The minibatches also
-// need 32 days in groups that are half full on average: a launch costs what its
-// blocks do, and a block the same for 1 as for 16 days (50 ODs, 200 links, 288
-// intervals, an epoch: 16 days 160 one day per block against 170, 30 days 219
-// against 174, 100 days 469 against 252; in 4 clusters 167 against 189, 226
-// against 204, 487 against 263).
-constexpr int64_t kMinPassProducts = int64_t(1) << 21;
+// days per block run: a whole pass below 2^22 and a minibatch's epoch below 2^20
+// is launches and latency, where one day per block is faster (loss passes of
+// 0.9 M: 42 against 43 us, of 2.3 M 47 against 46, of 5.2 M 99 against 68; a
+// check of 2.6 M in 24 intervals 165 against 175; epochs of 0.75 M 79 against 92
+// us, of 1.0 M 120 against 117).  The minibatches also need 32 days in groups
+// that are half full on average: a launch costs what its blocks do, and a block
+// the same for 1 as for 16 days (50 ODs, 200 links, 288 intervals, an epoch: 16
+// days 160 one day per block against 170, 30 days 219 against 174, 100 days 469
+// against 252; in 4 clusters 167 against 189, 226 against 204, 487 against 263).
+constexpr int64_t kMinPassProducts = int64_t(1) << 22;
 constexpr int64_t kMinStepProducts = int64_t(1) << 20;
 constexpr int32_t kMinStepDays = 32;
 // handles with packed union tiles: at most this many clusters and bytes

@@ -110,8 +110,12 @@ k_dense_resid(int32_t n, int32_t nr, const int32_t* __restrict__ rows, const S* 
 // 4.1 against 4.8 us for 500 x 500, where a block has only its own latency to
 // wait for.  A grid that fills the chip several times hides the two loads
 // before each row, and pays for the block's first barrier: 23.7 against 24.5 us
-// for 6000 x 6000.  The line lies at two blocks per CU.
-constexpr int64_t kLdsBlocks = 512;
+// for 6000 x 6000.  The line lies at two blocks per CU, for FP64 (half the
+// columns per block) at one; 20 epochs with and without LDS: FP32 n = 1500 (72
+// blocks) 306 and 345 us, 4000 (512) 585 and 595; FP64 1500 (144) 348 and 379,
+// 2300 (324) 501 and 498, 4000 (1024) 943 and 934; bf16 4000 (256) 446 and 475.
+template <typename S>
+constexpr int64_t kLdsBlocks = sizeof(S) == 8 ? 256 : 512;
 template <typename S, bool LDS>
 struct SliceRows {
   int32_t row[LDS ? kSliceRows : 1];
@@ -410,7 +414,7 @@ hipError_t run(const DenseArgs& a, hipStream_t s) {
         auto go = [&](auto kern) {
           hipLaunchKernelGGL(kern, grid, dim3(kBlock), 0, s, a.n, nr, rows, B, r, by_row, part);
         };
-        if ((int64_t)grid.x * grid.y <= kLdsBlocks)
+        if ((int64_t)grid.x * grid.y <= kLdsBlocks<S>)
           go(k_dense_colsum<S, VEC, true>);
         else
           go(k_dense_colsum<S, VEC, false>);
@@ -433,7 +437,7 @@ hipError_t run_bf16(const DenseArgs& a, hipStream_t s) {
         auto go = [&](auto kern) {
           hipLaunchKernelGGL(kern, grid, dim3(kBlock), 0, s, a.n, nr, rows, B, r, by_row, part);
         };
-        if ((int64_t)grid.x * grid.y <= kLdsBlocks)
+        if ((int64_t)grid.x * grid.y <= kLdsBlocks<float>)
           go(k_dense_colsum_bf16<VEC, true>);
         else
           go(k_dense_colsum_bf16<VEC, false>);

@@ -1064,7 +1064,15 @@ bool mfma_fwd_shares(const dode_dar* dar, int32_t day_tile, bool corr) {
 template <int MODE, int NT>
 hipError_t launch_fwd(const dode_dar* dar, const ChunkSched& cs, const WaveWork* wt, int64_t n,
                       const Layout& ly, const float* Q, const float* X, float* R, hipStream_t s) {
-  if (mfma_fwd_shares(dar, 16 * NT, MODE == kFP8Corr)) {
+  // Sharing pays where the loads of the demand, or its split, cost more than the
+  // block's barriers.  FP8 scales every demand value it loads: from 4 k-steps per
+  // tile and row of lags on (6: an epoch in 114 against 139 us, 5.5: a launch in 13.8
+  // against 17.2; 2: an epoch in 28 against 27).  Else it takes a launch that fills the chip
+  // three times (2432 blocks 49.8 against 58.8 us, 512 and 640 blocks 0.98 to 1.06
+  // times as fast, below 0.94 to 1.02).
+  const bool pays = MODE == kFP8 ? dar->dims.K * (int64_t)dar->tiles.kf_total >= 4 * dar->tiles.nLT
+                                 : n >= 768 * kFwdWaves;
+  if (pays && mfma_fwd_shares(dar, 16 * NT, MODE == kFP8Corr)) {
     const int64_t lag_bytes = fwd_lag_bytes(dar, 16 * NT);
     const int lags = (int)std::max<int64_t>(1, std::min<int64_t>(dar->dims.K, kFwdStage / lag_bytes));
     const int64_t nblk = n / kFwdWaves;

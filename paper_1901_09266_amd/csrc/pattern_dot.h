@@ -257,16 +257,4 @@ __device__ __forceinline__ S col_dot(const DevPat& pt, const DevVals& v, int c, 
   return acc;
 }
 
-// col_dot for the minibatch at positions first..first+bh-1 of a permutation
-// with inverse pos_c (nullptr: every interval, slot h).
-template <int ST, typename S>
-__device__ __forceinline__ S col_dot_chunk(const DevPat& pt, const DevVals& v, int c, int t, int p,
-                                           const int32_t* pos_c, int32_t first, int32_t bh,
-                                           const S* Rd, int64_t r_s, int64_t r_b) {
-  return col_dot<ST, S>(pt, v, c, t, p, [&](int l) {
-    const int s = pos_c ? pos_c[t + l] - first : t + l;
-    return s < bh ? s : -1;
-  }, Rd, r_s, r_b);
-}
-
 }  // namespace

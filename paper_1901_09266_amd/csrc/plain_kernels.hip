@@ -198,6 +198,9 @@ k_apply_rows(DevPat pt, DevVals v, const int32_t* day_cluster, int32_t cluster, 
   }
 }
 
+// One wave per departure interval and day.  (col_walk over every lag with a wave
+// per slice was slower, 23.0 against 20.9 us for 18 days of 26 ODs, 483 links, 24
+// intervals, 6 lags: its registers cost waves, and the residuals come from memory.)
 template <int ST, typename S>
 __global__ void __launch_bounds__(kAdjBlock)
 k_adjoint_rows(DevPat pt, DevVals v, const int32_t* day_cluster, int32_t cluster, Layout ly,
@@ -207,7 +210,7 @@ k_adjoint_rows(DevPat pt, DevVals v, const int32_t* day_cluster, int32_t cluster
   const S* Rd = R + d * ly.r_d;
   for (int p = threadIdx.x; p < pt.P; p += kAdjBlock)
     G[d * ly.q_d + t * ly.q_t + col_at(p, ly.q_b)] =
-        col_dot_chunk<ST, S>(pt, v, c, t, p, nullptr, 0, pt.H, Rd, ly.r_s, ly.r_b);
+        col_dot<ST, S>(pt, v, c, t, p, [&](int l) { return t + l; }, Rd, ly.r_s, ly.r_b);
 }
 
 // One wave per day: lane i takes partials i, i+64, ..., then a butterfly (fixed

@@ -50,13 +50,13 @@ def run_all(dar, Q, X):
     (1100, 40, 4, 4, 3, 8),      # demand rows a lag at a time, unions of many column runs
     (6, 2600, 3, 3, 2, 5),       # lines too long to stage: one-day kernels
     (4, 1400, 2, 2, 1, 3),       # too long in FP64 only
-    # the same edges in passes large enough for the matrix cores (2^21 products)
-    (12, 14, 1200, 1202, 3, 70),
-    (64, 128, 260, 260, 2, 16),
+    # the same edges in passes large enough for the matrix cores (2^22 products)
+    (12, 14, 2400, 2402, 3, 70),
+    (64, 128, 300, 300, 2, 16),
     (65, 129, 200, 198, 5, 17),
     (30, 1030, 100, 100, 3, 9),
-    (1100, 40, 60, 60, 3, 8),
-    (4, 1400, 250, 250, 1, 30),
+    (1100, 40, 80, 80, 3, 8),
+    (4, 1400, 250, 250, 1, 60),
 ])
 def test_days_match_oracle_and_single_days(storage, P, L, T, H, K, n):
     inst = make_instance(P=P, L=L, T=T, H=H, K=K, sizes=(n,), inc=1.0 if P == 1 else 0.06,
@@ -153,7 +153,7 @@ def test_plan_nonfinite_values_stay_on_the_pattern(storage, T):
 
 
 @pytest.mark.parametrize("storage", ["f64", "f32", "bf16"])
-@pytest.mark.parametrize("T", [8, 400])   # one day per block, 16 days per block
+@pytest.mark.parametrize("T", [8, 700])   # one day per block, 16 days per block
 def test_nonfinite_values_stay_on_the_pattern(storage, T):
     """A NaN or infinite demand or count of one day reaches the entries that
     the pattern connects it to, of that day, and no other."""

@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 
 
 def solve(inst, dar, perms, **kw):
-    p = dode.make_params(epochs=2, batch_rows=3 * inst.L, eta=5.0, **kw)
+    rows = 3 if inst.H < 50 else 60
+    p = dode.make_params(epochs=2, batch_rows=rows * inst.L, eta=5.0, **kw)
     plan = dode.spgd_plan_create(dar, inst.day_cluster, p, perm=perms)
     Q = torch.zeros((inst.D, inst.T, inst.P), dtype=torch.float32, device="cuda")
     A = torch.zeros_like(Q)
@@ -35,6 +36,10 @@ def solve(inst, dar, perms, **kw):
     (260, 300, 6, 6, 3, (20,), 0.05, "bernoulli"),       # every OD in a block; one lag per phase at 64 days
     (600, 70, 5, 5, 3, (9,), 0.05, "bernoulli"),         # one lag fits at 16 days only
     (1100, 40, 4, 4, 2, (5,), 0.05, "bernoulli"),        # too long: one wave per tile group
+    # launches large enough that bf16 and corrected values share the demand too
+    (40, 129, 200, 200, 3, (33, 130), 0.1, "corridor"),
+    (150, 264, 120, 118, 12, (170,), 0.08, "corridor"),
+    (260, 300, 100, 100, 3, (400,), 0.05, "bernoulli"),
 ])
 def test_forward_blocks_give_the_one_launch_bits(storage, refine, P, L, T, H, K, sizes, inc, pattern):
     inst = make_instance(P=P, L=L, T=T, H=H, K=K, sizes=sizes, inc=inc, pattern=pattern,
