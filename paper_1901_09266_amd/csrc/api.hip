@@ -1607,7 +1607,7 @@ dode_status dode_dar_patterns_from_speeds(int32_t n_paths, const int32_t* path_p
       return fail(DODE_ERR_ARG, "DODE_DAR_SCRATCH_BYTES='%s' is not a positive byte count", e);
     limit = (size_t)v;
   }
-  if (dar_fused(f64 != 0, n_paths, longest, H, H_speed, K, n_patterns)) {   // no scratch
+  if (dar_fused_patterns(f64 != 0, n_paths, longest, H, H_speed, K) > 0) {   // no scratch
     HIP_TRY(dar_ratios(f64 != 0, n_paths, path_ptr, path_link, n_pairs, longest, L, link_len, speed,
                        n_patterns, pattern_ptr, H_speed, dt, H, K, Rr, cost, s));
     return DODE_OK;

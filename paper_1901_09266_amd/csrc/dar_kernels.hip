@@ -468,8 +468,11 @@ hipError_t run_fused(int32_t n_paths, const int32_t* path_ptr, const int32_t* pa
   const int nw = std::max(1, (longest + SEG - 1) / SEG);
   const int64_t per = (int64_t)n_paths * ((H + 62) / 63);
   const size_t lds = (size_t)2 * nw * ND * 64 * sizeof(S);
-  for (int32_t q0 = 0; q0 < n_patterns; q0 += kPatterns) {
-    const int32_t nq = std::min(kPatterns, n_patterns - q0);
+  const int32_t per_launch =
+      dar_fused_patterns(sizeof(S) == 8, n_paths, longest, H, H_speed, K);
+  if (per_launch < 1) return hipErrorInvalidValue;
+  for (int32_t q0 = 0; q0 < n_patterns; q0 += per_launch) {
+    const int32_t nq = std::min(per_launch, n_patterns - q0);
     PatternDays pd{};
     for (int32_t q = 0; q <= nq; ++q) pd.ptr[q] = pattern_ptr[q0 + q];
     hipLaunchKernelGGL((k_ratios<S, KMAX, SEG, ND>), dim3((unsigned)(per * nq)), dim3(64 * nw), lds,
@@ -554,12 +557,15 @@ hipError_t dar_from_speeds(bool f64, int32_t n_paths, const int32_t* path_ptr,
                     static_cast<float*>(exit_time), sums, static_cast<float*>(cost), s);
 }
 
-bool dar_fused(bool f64, int32_t n_paths, int32_t longest, int32_t H, int32_t H_speed, int32_t K,
-               int32_t n_patterns) {
+int32_t dar_fused_patterns(bool f64, int32_t n_paths, int32_t longest, int32_t H, int32_t H_speed,
+                           int32_t K) {
   const int seg = f64 ? (K <= 8 ? Seg<double, 8>::kLinks : Seg<double, 16>::kLinks)
                       : (K <= 8 ? Seg<float, 8>::kLinks : Seg<float, 16>::kLinks);
-  const int64_t blocks = (int64_t)n_paths * ((H + 62) / 63) * std::min(n_patterns, kPatterns);
-  return longest <= seg * kMaxSegs && blocks <= INT32_MAX && H_speed <= (1 << 24);
+  if (longest > seg * kMaxSegs || H_speed > (1 << 24)) return 0;
+  // a block per path and 63 intervals, a wave per segment of the longest path
+  const int64_t threads =
+      (int64_t)n_paths * (((int64_t)H + 62) / 63) * 64 * std::max(1, (longest + seg - 1) / seg);
+  return (int32_t)std::min<int64_t>(kPatterns, kGridThreads / threads);
 }
 
 hipError_t dar_ratios(bool f64, int32_t n_paths, const int32_t* path_ptr, const int32_t* path_link,

@@ -367,6 +367,10 @@ struct DayList {
   int32_t n, nd, cluster, n_days;
 };
 
+// Most threads of a launch along one dimension of its grid (HIP counts them in
+// 32 bits and refuses more).
+constexpr int64_t kGridThreads = UINT32_MAX;
+
 // Zeroed elements past the end of each plan state array (X, Q, A, R).
 constexpr int64_t kStatePad = 64;
 
@@ -620,9 +624,10 @@ hipError_t dar_from_speeds(bool f64, int32_t n_paths, const int32_t* path_ptr,
                            double* sums, void* cost, hipStream_t s);
 // The same for several patterns in one kernel without scratch (pattern_ptr host
 // [n_patterns+1]; Rr [n_patterns][K][H][n_pairs], cost [n_patterns][H][n_paths]
-// or nullptr); dar_fused: whether paths of up to `longest` links fit it
-bool dar_fused(bool f64, int32_t n_paths, int32_t longest, int32_t H, int32_t H_speed, int32_t K,
-               int32_t n_patterns);
+// or nullptr); dar_fused_patterns: the patterns of one launch, 0 where paths of
+// up to `longest` links, or a launch of one pattern, do not fit it
+int32_t dar_fused_patterns(bool f64, int32_t n_paths, int32_t longest, int32_t H, int32_t H_speed,
+                           int32_t K);
 hipError_t dar_ratios(bool f64, int32_t n_paths, const int32_t* path_ptr, const int32_t* path_link,
                       int64_t n_pairs, int32_t longest, int32_t L, const void* len,
                       const void* speed, int32_t n_patterns, const int32_t* pattern_ptr,

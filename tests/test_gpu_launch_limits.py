@@ -1,0 +1,34 @@
+"""GPU: calls whose work, in one launch, would pass HIP's limit of 2^32 - 1
+threads along a grid's x."""
+import numpy as np
+import pytest
+
+import paper_1901_09266_amd as dode
+from gpu_helpers import say
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def test_ratios_of_more_patterns_than_a_launch_can_take():
+    """262 200 paths, one of 128 links (blocks of 1024 threads), 16 patterns of
+    one day: 15 patterns fill a launch.  Each pattern alone gives the same bits."""
+    n_paths, L, H, C = 262_200, 130, 63, 16
+    say("ratio launch limit", n_paths, C)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    deg = torch.ones(n_paths, dtype=torch.int64, device="cuda")
+    deg[7] = 128
+    ptr = torch.zeros(n_paths + 1, dtype=torch.int32, device="cuda")
+    ptr[1:] = deg.cumsum(0)
+    link = torch.randint(0, L, (int(ptr[-1]),), generator=g, device="cuda", dtype=torch.int32)
+    length = torch.rand(L, generator=g, device="cuda") + 0.5
+    speed = torch.rand((C, L, H), generator=g, device="cuda") + 0.5
+    Rr, cost = dode.dode_dar_patterns_from_speeds(ptr, link, length, speed,
+                                                  np.arange(C + 1, dtype=np.int32), 5.0, H, 1,
+                                                  with_costs=True)
+    for q in (0, 7, 14, 15):
+        Rq, cq = dode.dode_dar_costs_from_speeds(ptr, link, length, speed[q:q + 1], 5.0, H, 1)
+        torch.cuda.synchronize()
+        assert torch.equal(Rr[q], Rq) and torch.equal(cost[q], cq)
+        assert (cost[q] > 0).all() and (Rr[q] >= 0).all()
