@@ -160,8 +160,10 @@ __device__ __forceinline__ S row_dot(const DevPat& pt, const DevVals& v, int c, 
 // lags ascending, a lag's entries in CSC order, from the OD-sliced layout; row(n, l)
 // is the residual row of the n-th set lag l.  `width` is the longest column of the
 // wave's slice.  Entries go in steps of 8, three steps' loads in flight;
-// `stage` runs once the first ones are issued.  Past the column's last entry that
-// one is read again and its product dropped.
+// `stage` runs once the first ones are issued.  Every lane reads `width` entries,
+// its column's and then the slice's padding, so a load is a run of memory (with
+// each lane's own last entry again instead, columns of unequal length cost 1.5
+// times as much); the products past the column's end are dropped.
 template <int ST, typename S, typename G, typename F>
 __device__ __forceinline__ S col_walk(const DevPat& pt, const DevVals& v, int c, int t, int slice,
                                       int32_t deg, int32_t s0, int32_t width, uint64_t mask,
@@ -178,7 +180,7 @@ __device__ __forceinline__ S col_walk(const DevPat& pt, const DevVals& v, int c,
     const E* WT = static_cast<const E*>(v.WT) + c * v.cstride_c + ((int64_t)l * pt.T + t) * pt.sc_len;
 #pragma unroll
     for (int u = 0; u < NE; ++u) {
-      const uint32_t slot = s0 + 64 * max(0, min(kf + u, deg - 1));
+      const uint32_t slot = s0 + 64 * min(kf + u, width - 1);
       w[b][u] = WT[slot];
       a[b][u] = pt.sc_row[slot];
     }

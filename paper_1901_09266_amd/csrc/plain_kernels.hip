@@ -106,6 +106,7 @@ k_chunk_adj_step(DevPat pt, DevVals v, const int32_t* day_cluster, int32_t clust
   const int slot_l = lane < pt.K ? dsc[kDescSlot + lane] : -1;
   const int slice = task - i * slices;
   const bool in = p < pt.P, adagrad = st.optimizer == 0;
+  const int column = min(lane, pt.P - 1 - 64 * slice);   // lanes past the last OD read its values
   const int32_t deg = in ? pt.col_ptr[p + 1] - pt.col_ptr[p] : 0;
   const int32_t off = pt.sc_off[slice];
   const int32_t width = ((slice + 1 < slices ? pt.sc_off[slice + 1] : (int32_t)pt.sc_len) - off) / 64;
@@ -118,7 +119,7 @@ k_chunk_adj_step(DevPat pt, DevVals v, const int32_t* day_cluster, int32_t clust
   S q = in ? Q[idx] : S(0), acc = in && adagrad ? A[idx] : S(0), g;
   if (__builtin_popcountll(mask) <= rows) {
     S* rs = reinterpret_cast<S*>(r_stage) + (int64_t)wave * rows * pt.L;
-    g = col_walk<ST, S>(pt, v, c, t, slice, deg, off + lane, width, mask, 4,
+    g = col_walk<ST, S>(pt, v, c, t, slice, deg, off + column, width, mask, 4,
                         [&](int n, int) { return rs + n * pt.L; }, [&] {
       S* to = rs;
       for (uint64_t m = mask; m;) {
@@ -150,7 +151,7 @@ k_chunk_adj_step(DevPat pt, DevVals v, const int32_t* day_cluster, int32_t clust
       __builtin_amdgcn_wave_barrier();
     });
   } else {
-    g = col_walk<ST, S>(pt, v, c, t, slice, deg, off + lane, width, mask, ly.r_b, [&](int, int l) {
+    g = col_walk<ST, S>(pt, v, c, t, slice, deg, off + column, width, mask, ly.r_b, [&](int, int l) {
       return Rd + (int64_t)__builtin_amdgcn_readlane(slot_l, l) * ly.r_s;
     }, [] {});
   }
