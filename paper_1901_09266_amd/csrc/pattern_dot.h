@@ -130,11 +130,13 @@ __device__ __forceinline__ S row_part(const DevPat& pt, const DevVals& v, int c,
 // (entries come in pairs).  ME is the longest row the form takes: up to 8
 // entries three lags' loads go out together, up to 16 two lags', beyond that
 // (ME = 0) eight entries of one lag (ME = -4: four, for kernels whose other work
-// needs the registers).
+// needs the registers).  any: false for a wave none of whose rows has entries.
 template <int ST, typename S, int ME, typename F>
 __device__ __forceinline__ S row_dot(const DevPat& pt, const DevVals& v, int c, int h, int32_t deg,
-                                     int32_t s0, const S* q, int64_t q_t, int64_t q_b, F&& stage) {
-  const int l_begin = max(0, h - pt.T + 1), l_end = min(pt.K, h + 1);   // t = h - l in [0, T)
+                                     int32_t s0, bool any, const S* q, int64_t q_t, int64_t q_b,
+                                     F&& stage) {
+  const int l_begin = max(0, h - pt.T + 1);   // t = h - l in [0, T)
+  const int l_end = any ? min(pt.K, h + 1) : l_begin;
   S acc = 0;
   if constexpr (ME > 0) {
     return row_part<ST, S, ME, ME == 8 ? 3 : 2>(pt, v, c, h, deg, s0, 0, l_begin, l_end, q, q_t, q_b,
@@ -152,8 +154,8 @@ __device__ __forceinline__ S row_dot(const DevPat& pt, const DevVals& v, int c, 
 template <int ST, typename S>
 __device__ __forceinline__ S row_dot(const DevPat& pt, const DevVals& v, int c, int h, int a,
                                      const S* q, int64_t q_t, int64_t q_b) {
-  return row_dot<ST, S, -4>(pt, v, c, h, pt.row_ptr[a + 1] - pt.row_ptr[a], pt.sr_first[a], q, q_t,
-                           q_b, [] {});
+  return row_dot<ST, S, -4>(pt, v, c, h, pt.row_ptr[a + 1] - pt.row_ptr[a], pt.sr_first[a], true, q,
+                           q_t, q_b, [] {});
 }
 
 // Column (t, p) of rho_c^T over the lags of `mask` (those whose rows are given),

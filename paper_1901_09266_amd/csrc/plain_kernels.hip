@@ -60,6 +60,9 @@ k_chunk_resid(DevPat pt, DevVals v, const int32_t* day_cluster, int32_t cluster,
   const int a = lane.x;
   const bool in = a >= 0;
   const int32_t deg = lane.y, s0 = lane.z;
+  // a slice's links come by degree: a first lane without entries is a wave
+  // without (the waves past the last slice are: half of a block with 83 links)
+  const bool any = __builtin_amdgcn_readfirstlane(deg) > 0;
   const S x = in ? X[d * ly.x_d + h * ly.x_h + col_at(a, ly.x_b)] : S(0);
   S xhat;
   if constexpr (STAGE) {
@@ -67,7 +70,7 @@ k_chunk_resid(DevPat pt, DevVals v, const int32_t* day_cluster, int32_t cluster,
     const S* qd = Q + d * ly.q_d;
     const unsigned inv = 0xffffffffu / (unsigned)pt.P + 1;   // i / P while i * P < 2^32 (P > 1)
     // row t = h - l of the staged copy sits at (h - t) * P: base h*P, stride -P
-    xhat = row_dot<ST, S, ME>(pt, v, c, h, deg, s0, qs + (int64_t)h * pt.P, -(int64_t)pt.P, 4, [&] {
+    xhat = row_dot<ST, S, ME>(pt, v, c, h, deg, s0, any, qs + (int64_t)h * pt.P, -(int64_t)pt.P, 4, [&] {
       for (int i = threadIdx.x; i < pt.K * pt.P; i += kRowsBlock) {
         const int l = pt.P > 1 ? (int)__umulhi((unsigned)i, inv) : i, p = i - l * pt.P, t = h - l;
         qs[i] = (t >= 0 && t < pt.T) ? qd[(int64_t)t * ly.q_t + col_at(p, ly.q_b)] : S(0);
@@ -75,7 +78,7 @@ k_chunk_resid(DevPat pt, DevVals v, const int32_t* day_cluster, int32_t cluster,
       __syncthreads();
     });
   } else {
-    xhat = row_dot<ST, S, ME>(pt, v, c, h, deg, s0, Q + d * ly.q_d, ly.q_t, ly.q_b, [] {});
+    xhat = row_dot<ST, S, ME>(pt, v, c, h, deg, s0, any, Q + d * ly.q_d, ly.q_t, ly.q_b, [] {});
   }
   if (in) R[d * ly.r_d + s * ly.r_s + col_at(a, ly.r_b)] = xhat - x;
 }
@@ -354,14 +357,26 @@ struct RunResid {
       hipLaunchKernelGGL(kern, grid, dim3(kRowsBlock), lds, s, dar->pat(), dar->vals(), dc, cl, cs,
                          ly, static_cast<const S*>(Q), static_cast<const S*>(X), static_cast<S*>(R));
     };
+    // The forms of 8 and 16 entries hide latency at 60 to 150 registers, 3 to 8
+    // blocks a CU.  A launch of more blocks than that is better off with four
+    // entries of a lag at a time where their entries are mostly padding (links of
+    // 2.5 ODs, at most 9: 96 intervals of 60 days in FP64 37 against 51 us an
+    // epoch, of 4 days 20 either way; links of 5 ODs, at most 14: 40 intervals of
+    // 365 days in FP32 1484 against 1349), and for the 16 in FP8, whose codes cost
+    // most to widen (40 intervals of 60 days 461 against 509, 10 870 against 750).
+    const int64_t me = dar->max_row <= 8 ? 8 : 16;
+    const bool fills = (int64_t)grid.x * grid.y * grid.z >= 1024;
+    const bool padded = me * dar->dims.L > 5 * dar->nnz || (me == 16 && ST == DODE_FP8_E4M3);
     if (stage > kStageBytes)
       go(k_chunk_resid<ST, S, false, 0>, 0);
-    else if (dar->max_row <= 8)
-      go(k_chunk_resid<ST, S, true, 8>, stage);
-    else if (dar->max_row <= 16)
-      go(k_chunk_resid<ST, S, true, 16>, stage);
-    else
+    else if (dar->max_row > 16)
       go(k_chunk_resid<ST, S, true, 0>, stage);
+    else if (fills && padded)
+      go(k_chunk_resid<ST, S, true, -4>, stage);
+    else if (me == 8)
+      go(k_chunk_resid<ST, S, true, 8>, stage);
+    else
+      go(k_chunk_resid<ST, S, true, 16>, stage);
     return hipGetLastError();
   }
 };
