@@ -327,12 +327,14 @@ dode_status dar_logits_bwd(const dode_routes* routes, int32_t f64, const void* R
  *   f64: nonzero for double arrays, else float.  K <= 16.
  * Errors: DODE_ERR_SHAPE for malformed path tables, DODE_ERR_ARG for
  * non-positive or non-finite lengths or speeds.  Synchronises `stream` (the
- * path tables and the checks are read back).  Paths of more than 128 links
- * (64 with K > 8; half of that with f64) use a scratch buffer of at
- * most 4 GiB (the trajectories of a chunk of days), or of the byte count in
- * the environment variable DODE_DAR_SCRATCH_BYTES (smaller values process
- * fewer days at a time; a value that is not a positive integer is
- * DODE_ERR_ARG for any path length).  The results do not depend on the chunking beyond the
+ * path tables and the checks are read back).  Calls with paths of more than 128
+ * links (64 with K > 8; half of that with f64), or of few long paths, use a
+ * scratch buffer of at most 4 GiB (the trajectories of a chunk of days), or of
+ * the byte count in the environment variable DODE_DAR_SCRATCH_BYTES (smaller
+ * values process fewer days at a time; a value that is not a positive integer is
+ * DODE_ERR_ARG for any path length).  Calls of few paths and many days use at
+ * most 64 MiB, and none where the variable allows less than they need.  The
+ * results do not depend on either split of the days beyond the
  * rounding of the running day sums.
  */
 dode_status dode_dar_from_speeds(int32_t n_paths, const int32_t* path_ptr,
@@ -349,8 +351,8 @@ dode_status dode_dar_from_speeds(int32_t n_paths, const int32_t* path_ptr,
  *   cost [H][n_paths] (output, device, may be NULL): for departure interval t,
  *       the mean over the n_days days of the time to cross the whole path when
  *       leaving at t*dt (days summed in FP64).
- * The scratch of long paths grows by n_paths*(H+1) values per day of a chunk
- * and an FP64 array of n_paths*H.
+ * The trajectory scratch grows by n_paths*(H+1) values per day of a chunk and an
+ * FP64 array of n_paths*H.
  */
 dode_status dode_dar_costs_from_speeds(int32_t n_paths, const int32_t* path_ptr,
                                        const int32_t* path_link, int64_t n_pairs, int32_t L,

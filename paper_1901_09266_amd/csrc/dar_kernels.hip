@@ -211,6 +211,8 @@ k_dar_windows(int64_t n_pairs, int32_t n_days_chunk, int32_t H, int32_t K, S dt,
 // form a pipeline over the groups of days, one step per barrier.  The speed
 // gathers of a link are in flight while its windows are added.  Days are added
 // in order, so the results are those of the two kernels above for any grouping.
+// Where the blocks are too few to fill the chip (ratio_parts), the days of a
+// pattern are split over gridDim.y parts, whose sums k_join_parts adds in order.
 //
 // What bounds it: the VALU (about 45 instructions per day, link and boundary
 // in FP32) and the chain of gathers along a path.  The trajectories of the two
@@ -243,7 +245,8 @@ __global__ void __launch_bounds__(64 * kMaxSegs)
 k_ratios(int32_t n_paths, const int32_t* __restrict__ path_ptr,
          const int32_t* __restrict__ path_link, int32_t L, const S* __restrict__ len,
          const S* __restrict__ speed, PatternDays days, int32_t H_speed, S dt, S rdt, int32_t H,
-         int32_t K, int64_t n_pairs, S* __restrict__ Rr, S* __restrict__ cost) {
+         int32_t K, int64_t n_pairs, S* __restrict__ Rr, S* __restrict__ cost,
+         double* __restrict__ part_exit, S* __restrict__ part_sum) {
 #pragma clang fp contract(off)   // as in k_trajectories
   constexpr int kWin = 63;
   extern __shared__ __align__(16) unsigned char hand_mem[];
@@ -255,7 +258,11 @@ k_ratios(int32_t n_paths, const int32_t* __restrict__ path_ptr,
   const int chunk = item % n_chunks;
   item /= n_chunks;
   const int k = item % n_paths, q = item / n_paths;
-  const int d_begin = days.ptr[q], n_days = days.ptr[q + 1] - d_begin;
+  // the block's days: whole groups, a part of the pattern's
+  const int all = days.ptr[q + 1] - days.ptr[q];
+  const int per = ((all + ND - 1) / ND + gridDim.y - 1) / gridDim.y * ND;
+  const int skip = min(all, (int)blockIdx.y * per);
+  const int d_begin = days.ptr[q] + skip, n_days = min(per, all - skip);
   const int m0 = path_ptr[k], m_end = path_ptr[k + 1];
   const int n_segs = max(1, (m_end - m0 + SEG - 1) / SEG);
   const int m = m0 + wave * SEG;   // first pair of the wave's segment
@@ -345,6 +352,19 @@ k_ratios(int32_t n_paths, const int32_t* __restrict__ path_ptr,
   }
   const int h = chunk * kWin + lane;   // the lane's interval
   if (lane == kWin || h >= H) return;
+  if (gridDim.y > 1) {
+    const int64_t row = (int64_t)blockIdx.y * (gridDim.x / (n_paths * n_chunks)) + q;
+    if (wave == n_segs - 1) part_exit[(row * H + h) * n_paths + k] = exit_sum;
+#pragma unroll
+    for (int l = 0; l < KMAX; ++l)
+      if (l < K) {
+        S* out = part_sum + ((row * K + l) * H + h) * n_pairs + m;
+#pragma unroll
+        for (int i = 0; i < SEG; ++i)
+          if (i < n_links) out[i] = acc[i][l];
+      }
+    return;
+  }
   if (cost && wave == n_segs - 1)
     cost[((int64_t)q * H + h) * n_paths + k] = static_cast<S>(exit_sum / n_days);
   const int kk = min(K, H - h);   // lags that stay inside the day
@@ -357,6 +377,30 @@ k_ratios(int32_t n_paths, const int32_t* __restrict__ path_ptr,
         if (i < n_links) out[i] = l >= kk ? S(0) : acc[i][l] / static_cast<S>(n_days);
     }
   }
+}
+
+// Means over the days of pattern blockIdx.y from the sums of its parts: ratios
+// (idx below K*H*n_pairs), then path costs.
+template <typename S>
+__global__ void __launch_bounds__(kBlock)
+k_join_parts(int32_t n_parts, PatternDays days, int32_t n_paths, int64_t n_pairs, int32_t H, int32_t K,
+             const double* __restrict__ part_exit, const S* __restrict__ part_sum,
+             S* __restrict__ Rr, S* __restrict__ cost) {
+  const int q = blockIdx.y, nq = gridDim.y, n_days = days.ptr[q + 1] - days.ptr[q];
+  const int64_t n_r = (int64_t)K * H * n_pairs, n_c = (int64_t)H * n_paths;
+  int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i < n_r) {
+    const int l = (int)(i / (H * n_pairs)), h = (int)(i / n_pairs % H);
+    S s = S(0);
+    for (int p = 0; p < n_parts; ++p) s += part_sum[((int64_t)p * nq + q) * n_r + i];
+    Rr[q * n_r + i] = l >= min(K, H - h) ? S(0) : s / static_cast<S>(n_days);
+    return;
+  }
+  i -= n_r;
+  if (!cost || i >= n_c) return;
+  double s = 0.0;
+  for (int p = 0; p < n_parts; ++p) s += part_exit[((int64_t)p * nq + q) * n_c + i];
+  cost[q * n_c + i] = static_cast<S>(s / n_days);
 }
 
 template <typename S>
@@ -463,7 +507,8 @@ template <typename S, int KMAX>
 hipError_t run_fused(int32_t n_paths, const int32_t* path_ptr, const int32_t* path_link,
                      int64_t n_pairs, int32_t longest, int32_t L, const S* len, const S* speed,
                      int32_t n_patterns, const int32_t* pattern_ptr, int32_t H_speed, S dt,
-                     int32_t H, int32_t K, S* Rr, S* cost, hipStream_t s) {
+                     int32_t H, int32_t K, S* Rr, S* cost, int32_t n_parts, void* parts,
+                     hipStream_t s) {
   constexpr int SEG = Seg<S, KMAX>::kLinks, ND = Seg<S, KMAX>::kDays;
   const int nw = std::max(1, (longest + SEG - 1) / SEG);
   const int64_t per = (int64_t)n_paths * ((H + 62) / 63);
@@ -475,11 +520,17 @@ hipError_t run_fused(int32_t n_paths, const int32_t* path_ptr, const int32_t* pa
     const int32_t nq = std::min(per_launch, n_patterns - q0);
     PatternDays pd{};
     for (int32_t q = 0; q <= nq; ++q) pd.ptr[q] = pattern_ptr[q0 + q];
-    hipLaunchKernelGGL((k_ratios<S, KMAX, SEG, ND>), dim3((unsigned)(per * nq)), dim3(64 * nw), lds,
-                       s, n_paths, path_ptr, path_link, L, len, speed, pd, H_speed, dt,
-                       static_cast<S>(1) / dt, H, K, n_pairs,
-                       Rr + (int64_t)q0 * K * H * n_pairs,
-                       cost ? cost + (int64_t)q0 * H * n_paths : nullptr);
+    double* exits = static_cast<double*>(parts);
+    S* sums = reinterpret_cast<S*>(exits + (int64_t)n_parts * nq * H * n_paths);
+    S* rq = Rr + (int64_t)q0 * K * H * n_pairs;
+    S* cq = cost ? cost + (int64_t)q0 * H * n_paths : nullptr;
+    hipLaunchKernelGGL((k_ratios<S, KMAX, SEG, ND>), dim3((unsigned)(per * nq), n_parts), dim3(64 * nw),
+                       lds, s, n_paths, path_ptr, path_link, L, len, speed, pd, H_speed, dt,
+                       static_cast<S>(1) / dt, H, K, n_pairs, rq, cq, exits, sums);
+    if (n_parts > 1)
+      hipLaunchKernelGGL(k_join_parts<S>,
+                         dim3(blocks_for((int64_t)K * H * n_pairs + (int64_t)H * n_paths), nq),
+                         dim3(kBlock), 0, s, n_parts, pd, n_paths, n_pairs, H, K, exits, sums, rq, cq);
   }
   return hipGetLastError();
 }
@@ -488,12 +539,13 @@ template <typename S>
 hipError_t fused(int32_t n_paths, const int32_t* path_ptr, const int32_t* path_link,
                  int64_t n_pairs, int32_t longest, int32_t L, const void* len, const void* speed,
                  int32_t n_patterns, const int32_t* pattern_ptr, int32_t H_speed, double dt,
-                 int32_t H, int32_t K, void* Rr, void* cost, hipStream_t s) {
+                 int32_t H, int32_t K, void* Rr, void* cost, int32_t n_parts, void* parts,
+                 hipStream_t s) {
   auto go = [&](auto kmax) {
     return run_fused<S, decltype(kmax)::value>(
         n_paths, path_ptr, path_link, n_pairs, longest, L, static_cast<const S*>(len),
         static_cast<const S*>(speed), n_patterns, pattern_ptr, H_speed, static_cast<S>(dt), H, K,
-        static_cast<S*>(Rr), static_cast<S*>(cost), s);
+        static_cast<S*>(Rr), static_cast<S*>(cost), n_parts, parts, s);
   };
   if (K <= 3) return go(std::integral_constant<int, 3>{});
   if (K <= 6) return go(std::integral_constant<int, 6>{});
@@ -568,13 +620,45 @@ int32_t dar_fused_patterns(bool f64, int32_t n_paths, int32_t longest, int32_t H
   return (int32_t)std::min<int64_t>(kPatterns, kGridThreads / threads);
 }
 
+size_t dar_part_bytes(bool f64, int32_t n_paths, int64_t n_pairs, int32_t H, int32_t K,
+                      int32_t n_patterns) {
+  return (size_t)std::min(n_patterns, kPatterns) * H *
+         ((size_t)K * n_pairs * (f64 ? 8 : 4) + (size_t)n_paths * 8);
+}
+
+int32_t dar_parts(bool f64, int32_t n_paths, int32_t longest, int32_t H, int32_t K,
+                  int32_t n_patterns, int32_t most_days, size_t part_bytes, size_t traj_bytes) {
+  // A block takes the days of its pattern one group after the other, 5 to 13 us a
+  // group, and a group passes through a segment of links after the other.  Up to
+  // a block per CU the groups are split for two blocks per CU, at least four
+  // groups to a part, where that saves more than the parts cost (whole calls with
+  // the splits, without, and in the two kernels; 20 links, 288 intervals, FP32:
+  // 365 days, 1 path 198, 713 and 332 us, 10 paths 273, 718 and 647, 30 paths 419,
+  // 721 and 677, 50 paths 522, 721 and 816; 1095 days, 10 paths 442, 1934 and 1122).
+  const int seg = f64 ? (K <= 8 ? Seg<double, 8>::kLinks : Seg<double, 16>::kLinks)
+                      : (K <= 8 ? Seg<float, 8>::kLinks : Seg<float, 16>::kLinks);
+  const int nd = f64 ? (K <= 8 ? Seg<double, 8>::kDays : Seg<double, 16>::kDays) : Seg<float, 8>::kDays;
+  const int64_t blocks = (int64_t)n_paths * (((int64_t)H + 62) / 63) * std::min(n_patterns, kPatterns);
+  const int64_t groups = ((int64_t)most_days + nd - 1) / nd;
+  if (blocks > 256) return 1;
+  int64_t parts = std::max<int64_t>(1, std::min(512 / blocks, groups / 4));
+  parts = std::min(parts, std::max<int64_t>(1, (int64_t)((size_t(64) << 20) / part_bytes)));
+  const double saved = (groups - (groups + parts - 1) / parts) * (2.0 + 1.4 * std::min(longest, seg));
+  if (saved < 50.0 + 6e-6 * part_bytes * parts) parts = 1;   // us: sums, launch, allocation
+  // Few days of long paths are mostly segments; the two kernels take links side
+  // by side, but the patterns in turn, and trajectories have to be allocated.
+  const int64_t segs = (longest + seg - 1) / seg - 1, steps = (groups + parts - 1) / parts + segs;
+  if (blocks <= 128 && segs >= 8 && steps >= 15 * (int64_t)n_patterns && traj_bytes <= (size_t(64) << 20)) return 0;
+  return (int32_t)parts;
+}
+
 hipError_t dar_ratios(bool f64, int32_t n_paths, const int32_t* path_ptr, const int32_t* path_link,
                       int64_t n_pairs, int32_t longest, int32_t L, const void* len,
                       const void* speed, int32_t n_patterns, const int32_t* pattern_ptr,
                       int32_t H_speed, double dt, int32_t H, int32_t K, void* Rr, void* cost,
-                      hipStream_t s) {
+                      int32_t n_parts, void* parts, hipStream_t s) {
   return f64 ? fused<double>(n_paths, path_ptr, path_link, n_pairs, longest, L, len, speed,
-                             n_patterns, pattern_ptr, H_speed, dt, H, K, Rr, cost, s)
+                             n_patterns, pattern_ptr, H_speed, dt, H, K, Rr, cost, n_parts, parts, s)
              : fused<float>(n_paths, path_ptr, path_link, n_pairs, longest, L, len, speed,
-                            n_patterns, pattern_ptr, H_speed, dt, H, K, Rr, cost, s);
+                            n_patterns, pattern_ptr, H_speed, dt, H, K, Rr, cost, n_parts, parts, s);
 }
