@@ -82,10 +82,11 @@ typedef struct {
   int32_t kernel_path; /* 0 = fastest available for the storage type (matrix-core
                           tiles for BF16 / FP8 when a cluster has more than 2
                           days or refine_steps > 0, a forward and an adjoint
-                          launch per minibatch; FP32 and FP64 from 32 days in
-                          clusters of several days, and 2^20 products an
-                          epoch, on FP32 / FP64 matrix-core products of the
-                          pattern; else the sparse kernels),
+                          launch per minibatch; FP32 and FP64 on FP32 / FP64
+                          matrix-core products of the pattern for 16 days a
+                          block where an estimate of both from the pattern's
+                          padding, the days and the minibatches takes these
+                          for the faster; else the sparse kernels),
                           1 = sparse pattern kernels, 2 = matrix-core tiles
                           with one launch per minibatch, one workgroup per
                           independent part of it, 3 = matrix-core tiles with
@@ -197,7 +198,9 @@ dode_status dode_apply(const dode_dar* dar, int32_t cluster, const void* Q, int3
                        void* Xhat, void* stream);
 
 /* loss[d] = || rho_c q_d - x_d ||^2 per day (eq. "nnls"), accumulated in FP64
- * in a fixed order (bitwise reproducible).  loss dev double [n]. */
+ * in an order fixed by the handle and n_days (the same call gives the same bits;
+ * a day's loss may differ in its last bits from that of a call with other days,
+ * by the rounding of an FP64 sum of H*L squares).  loss dev double [n]. */
 dode_status dode_loss(const dode_dar* dar, int32_t cluster, const void* Q, const void* X,
                       int32_t n_days, double* loss, void* stream);
 

@@ -20,19 +20,6 @@ namespace {
 
 // clusters of at most this many days use the sparse kernels under kernel_path 0
 constexpr int32_t kSparseDays = 2;
-// From how many products (entries * lags * intervals * days) the kernels of 16
-// days per block run: a whole pass below 2^22 and a minibatch's epoch below 2^20
-// is launches and latency, where one day per block is faster (loss passes of
-// 0.9 M: 42 against 43 us, of 2.3 M 47 against 46, of 5.2 M 99 against 68; a
-// check of 2.6 M in 24 intervals 165 against 175; epochs of 0.75 M 79 against 92
-// us, of 1.0 M 120 against 117).  The minibatches also need 32 days in groups
-// that are half full on average: a launch costs what its blocks do, and a block
-// the same for 1 as for 16 days (50 ODs, 200 links, 288 intervals, an epoch: 16
-// days 160 one day per block against 170, 30 days 219 against 174, 100 days 469
-// against 252; in 4 clusters 167 against 189, 226 against 204, 487 against 263).
-constexpr int64_t kMinPassProducts = int64_t(1) << 22;
-constexpr int64_t kMinStepProducts = int64_t(1) << 20;
-constexpr int32_t kMinStepDays = 32;
 // handles with packed union tiles: at most this many clusters and bytes
 constexpr int32_t kUnionClusters = 64;
 constexpr size_t kUnionBytes = size_t(16) << 30;
@@ -107,37 +94,28 @@ dode_status check_days(int32_t n_days) {
   return DODE_OK;
 }
 
-int64_t products(const dode_dar* dar, int32_t n_days) {
-  return dar->nnz * dar->dims.K * std::min<int64_t>(dar->dims.T * (int64_t)n_days, INT32_MAX);
-}
-
-// Days per block of a whole pass over n_days days: 16 on the matrix cores, or,
-// where a row of 16 days is too long to stage or the pass is small, 1.
-int32_t pass_days(const dode_dar* dar, int32_t n_days) {
-  return products(dar, n_days) < kMinPassProducts ? 1 : days_per_group(dar, n_days);
-}
-
 // rho_c Q (- X) of n_days days of one cluster in the caller's layout
 hipError_t apply_rows(const dode_dar* dar, int32_t cluster, const void* Q, const void* X, void* out,
                       double* part, int32_t n_days, hipStream_t s) {
-  const int32_t nd = pass_days(dar, n_days);
+  const int32_t nd = days_per_group(), groups = (n_days + nd - 1) / nd;
   const Layout ly = day_major(dar->dims);
-  if (nd == 1) return plain_apply_rows(dar, nullptr, cluster, ly, Q, X, out, part, n_days, s);
-  const DayList dl{nullptr, (n_days + nd - 1) / nd, nd, cluster, n_days};
+  if (!dar->d_PR || !day_groups_fit(dar, groups) || !group_rows_pay(dar, groups, 1, n_days, part != nullptr))
+    return plain_apply_rows(dar, nullptr, cluster, ly, Q, X, out, part, n_days, s);
+  const DayList dl{nullptr, groups, nd, cluster, n_days};
   return days_rows(dar, dl, nullptr, dar->dims.H, ly, Q, X, out, part, s);
 }
 
 // G = f * rho_c^T R of full residual rows R, the same way
 hipError_t adjoint_rows(const dode_dar* dar, int32_t cluster, const void* R, void* G, double f,
                         int32_t n_days, hipStream_t s) {
-  const int32_t nd = pass_days(dar, n_days);
+  const int32_t nd = days_per_group(), groups = (n_days + nd - 1) / nd;
   const Layout ly = day_major(dar->dims);
-  if (nd == 1) {
+  if (!dar->d_PR || !day_groups_fit(dar, groups) || !group_cols_pay(dar, groups, 1, n_days)) {
     const hipError_t e = plain_adjoint_rows(dar, nullptr, cluster, ly, R, G, n_days, s);
     if (e != hipSuccess || f == 1.0) return e;
     return scale_state(dar->storage == DODE_F64, G, (int64_t)n_days * dar->dims.T * dar->dims.P, f, s);
   }
-  const DayList dl{nullptr, (n_days + nd - 1) / nd, nd, cluster, n_days};
+  const DayList dl{nullptr, groups, nd, cluster, n_days};
   return days_cols(dar, dl, ly, R, G, f, s);
 }
 
@@ -1020,6 +998,20 @@ int64_t build_slices(int32_t n, const std::vector<int32_t>& ptr, bool ranked, bo
   return len;
 }
 
+// Entries that a walk of eight at a time takes: every slice of 64 lines as long as
+// its longest. Also the longest line.
+int64_t walk_slots(int32_t n, const std::vector<int32_t>& ptr, int32_t* longest) {
+  int64_t slots = 0;
+  *longest = 0;
+  for (int32_t i0 = 0; i0 < n; i0 += 64) {
+    int32_t width = 0;
+    for (int32_t i = i0; i < std::min(n, i0 + 64); ++i) width = std::max(width, ptr[i + 1] - ptr[i]);
+    slots += 512 * (int64_t)((width + 7) / 8);
+    *longest = std::max(*longest, width);
+  }
+  return slots;
+}
+
 }  // namespace
 
 dode_status dar_destroy(dode_dar* dar) {
@@ -1133,6 +1125,8 @@ dode_status dar_create_ex(const dode_dims* dims, int32_t n_clusters, const int32
   std::vector<int32_t> sr_off, sr_first, sr_pos, sc_off, sc_first, sc_pos;
   d->sr_len = build_slices(dm.L, d->h_row_ptr, true, true, sr_off, sr_first, sr_pos);
   d->sc_len = build_slices(dm.P, d->h_col_ptr, false, false, sc_off, sc_first, sc_pos);
+  d->row_slots = walk_slots(dm.L, d->h_row_ptr, &d->max_row);
+  d->col_slots = walk_slots(dm.P, d->h_col_ptr, &d->max_col);
   if (d->sr_len > INT32_MAX || d->sc_len > INT32_MAX) {
     dar_destroy(d.release());
     return fail(DODE_ERR_SHAPE, "pattern too large for the sliced layout");
@@ -1147,7 +1141,6 @@ dode_status dar_create_ex(const dode_dims* dims, int32_t n_clusters, const int32
       int32_t* ln = &lanes[(size_t)4 * (a / 64 * 64 + (sr_first[a] - sr_off[a / 64]) / 2)];
       ln[0] = a;
       ln[1] = row_ptr[a + 1] - row_ptr[a];
-      d->max_row = std::max(d->max_row, ln[1]);
       ln[2] = sr_first[a];
     }
     lanes.insert(lanes.end(), sr_first.begin(), sr_first.end());
@@ -1158,7 +1151,7 @@ dode_status dar_create_ex(const dode_dims* dims, int32_t n_clusters, const int32
     HIP_TRY(dev_copy(&d->d_sc_row, sc_row));
   }
 
-  const size_t esz = storage == DODE_F64 ? 8 : storage == DODE_F32 ? 4 : storage == DODE_BF16 ? 2 : 1;
+  const size_t esz = d->value_size = storage == DODE_F64 ? 8 : storage == DODE_F32 ? 4 : storage == DODE_BF16 ? 2 : 1;
   // union tiles and their packed values, for handles whose clusters hold
   // several days (with more clusters they are single days, and those handles
   // fill the memory); where they do not fit, the one-day kernels serve alone
@@ -1907,20 +1900,23 @@ dode_status spgd_plan_create(const dode_dar* dar, const int32_t* day_cluster, in
     return fail(DODE_ERR_UNSUPPORTED,
                 "kernel_path 3 runs the chunked adjoint (adj_order 2) with 16-day waves only");
   // day groups of the pattern kernels (FP32 and FP64 minibatches, loss history)
-  const int64_t work = products(dar, D);
-  int32_t nd = max_days > kSparseDays && work >= kMinStepProducts ? days_per_group(dar, max_days) : 1;
-  if (nd > 1) {
+  if (dar->d_PR) {
+    const int32_t nd = days_per_group();
     std::vector<int32_t> gc, gf, gn;
-    for (int32_t c = 0, start = 0; c < C; start += p->cluster_days[c++])
+    int32_t used = 0;   // clusters with days
+    for (int32_t c = 0, start = 0; c < C; start += p->cluster_days[c++]) {
+      used += p->cluster_days[c] > 0;
       for (int32_t f = 0; f < p->cluster_days[c]; f += nd) {
         gc.push_back(c);
         gf.push_back(start + f);
         gn.push_back(std::min(nd, p->cluster_days[c] - f));
       }
+    }
     p->days.n = (int32_t)gc.size();
     p->days.nd = nd;
-    p->step_days = params->kernel_path == 0 && D >= kMinStepDays && 2 * D >= nd * p->days.n;
-    p->loss_days = work >= kMinPassProducts;
+    const bool fit = day_groups_fit(dar, p->days.n);
+    p->step_days = fit && params->kernel_path == 0 && group_step_pays(dar, bh, p->mt, p->days.n, used, D);
+    p->loss_days = fit && group_rows_pay(dar, p->days.n, used, D, true);
     if (p->step_days || p->loss_days) {
       gc.insert(gc.end(), gf.begin(), gf.end());
       gc.insert(gc.end(), gn.begin(), gn.end());

@@ -562,13 +562,119 @@ hipError_t by_storage(const dode_dar* dar, F&& f) {
 
 }  // namespace
 
-int32_t days_per_group(const dode_dar* dar, int32_t n_days) {
+// ---- which form a call takes ----------------------------------------------
+// The one-day kernels cost what the days' entries cost, the 16-day kernels what
+// the union tiles do, padding included, for groups that may be nearly empty, and
+// small launches of either are a chain of round trips.  No single count decides
+// it: by products alone (2^22 a pass; 2^20 an epoch and 32 days in groups half
+// full) a loss over one day of 400 ODs, 1500 links, 96 intervals with 5%
+// independent incidence took 219 us against 94 one day per block (FP32), an epoch
+// of 32 days of 150 ODs, 500 links, 3% incidence in minibatches of 4 of 144
+// intervals 1444 against 558 us (FP64).  So both are estimated, in us, and the
+// smaller is taken.  The models were fitted to launches in 3 to 288 intervals of 1
+// to 200 days, 26 x 300 to 400 x 1500 networks with corridor and independent
+// incidence (standard deviation 0.2 to 0.35 of the time); the faster
+// form against the one taken, geometric means: 0.99 over 1704 epochs in FP32 and
+// FP64, 0.99 over 772 losses, 0.98 over 772 gradients in all four types.
+namespace {
+
+// Stored types in the order of dode_dtype.
+struct FormCost {
+  double row_step, row_stage, col_step, col_stage, col_base;   // 16 days, per block
+  double pass_row, pass_col, pass_chain;                       // one day, whole passes
+  double step_row, step_col;                                   // one day, minibatches
+};
+constexpr FormCost kCost[] = {
+    {0.19, 0.44, 0.22, 0.46, 9.0, 0.74, 1.05, 0.5, 0.35, 0.80},
+    {0.19, 0.20, 0.30, 0.12, 6.0, 0.56, 0.73, 0.5, 0.30, 0.49},
+    {0.18, 0.20, 0.22, 0.35, 5.0, 0.51, 0.72, 0.5, 0.30, 0.49},
+    {0.73, 0.15, 1.00, 0.50, 4.0, 0.62, 0.77, 0.7, 0.30, 0.49},
+};
+constexpr double kFullWaves = 3200;     // waves that keep their latency to themselves
+constexpr double kBytesPerUs = 5.0e6;   // packed values from memory
+// Whole passes take less than the model, which minibatches are most of: a gradient
+// of 400 ODs, 1500 links, 96 intervals, 1 day in FP32 53 us against 78 one day per
+// block, where the plain comparison takes the latter.
+constexpr double kPass = 0.8;
+
+// One launch of a 16-day kernel: `lags` lags of each of n_rows rows of `groups` day
+// groups in `clusters` clusters.  A block's longest wave takes `step` per column
+// run and lag and the block `stage` per 64 columns and lag it stages, again for
+// every round of its tiles where the lags do not fit at once; past kFullWaves
+// they queue. The packed values come from memory once per cluster.
+double group_launch(const dode_dar* dar, const DevUnion& un, int64_t len, int waves, bool split,
+                    double n_rows, int64_t groups, int64_t clusters, double lags, int cols, int kl,
+                    double step, double stage, double base) {
+  const double blocks = n_rows * groups;
+  const int rounds = (un.n_tiles + waves - 1) / waves;
+  const double parts =
+      split ? std::max(1.0, std::min<double>(rounds, std::floor(kFillBlocks / std::max(1.0, blocks)))) : 1.0;
+  const int w = std::min(un.n_tiles, waves);
+  const double again = lags <= kl ? 1.0 : std::ceil(rounds / parts);
+  const double block = step * (len / 256.0) * lags / w / parts + stage * lags * again * cols / 64.0 + base;
+  const double bytes = (double)clusters * n_rows * lags * len * dar->value_size;
+  return block * std::max(1.0, blocks * parts * w / kFullWaves) + bytes / kBytesPerUs;
+}
+
+double group_rows(const dode_dar* dar, double n_rows, int64_t groups, int64_t clusters, bool split) {
+  const FormCost& c = kCost[dar->storage];
+  const size_t rb = 16 * kDayTiles * (is_f64(dar) ? 8 : 4);
+  return group_launch(dar, dar->u_rows, dar->pr_len, kRowWaves, split, n_rows, groups, clusters,
+                      dar->dims.K, dar->dims.P, lag_chunk(dar->dims.K, dar->dims.P, rb), c.row_step,
+                      c.row_stage, 5.0);
+}
+
+double group_cols(const dode_dar* dar, double n_rows, int64_t groups, int64_t clusters, double lags,
+                  bool step) {
+  const FormCost& c = kCost[dar->storage];
+  const size_t rb = 16 * kDayTiles * (is_f64(dar) ? 8 : 4);
+  const int kl = lag_chunk(step ? std::min(2, dar->dims.K) : dar->dims.K, dar->dims.L, rb);
+  return group_launch(dar, dar->u_cols, dar->pc_len, kColWaves, true, n_rows, groups, clusters, lags,
+                      dar->dims.L, kl, c.col_step, c.col_stage, c.col_base);
+}
+
+// A link's (OD's) walk over its lags, eight entries a step, and the work of
+// n_rows rows of every day, in million slots.
+double row_chain(const dode_dar* dar) {
+  return (dar->dims.L + 255) / 256 * dar->dims.K * ((dar->max_row + 3) / 4);
+}
+double mega_slots(const dode_dar* dar, int64_t slots, double n_rows, int64_t days) {
+  return 1e-6 * slots * dar->dims.K * n_rows * days;
+}
+
+}  // namespace
+
+bool day_groups_fit(const dode_dar* dar, int64_t groups) {
   const size_t lines = std::max(dar->dims.P, dar->dims.L);
   const size_t rb = 16 * kDayTiles * (is_f64(dar) ? 8 : 4);
-  // a staged row has to fit, and every group of every row is a block of one launch
-  if (!dar->d_PR || lines * rb > kLdsBytes || (int64_t)std::max(dar->dims.H, dar->dims.T) * n_days > INT32_MAX - 8)
-    return 1;
-  return 16 * kDayTiles;
+  // a staged row has to fit, and a launch of all groups
+  return lines * rb <= kLdsBytes &&
+         std::max(dar->dims.H, dar->dims.T) * groups * 16 <= INT32_MAX - 8;
+}
+
+int32_t days_per_group() { return 16 * kDayTiles; }
+
+bool group_rows_pay(const dode_dar* dar, int64_t groups, int64_t clusters, int64_t days, bool sums) {
+  const FormCost& c = kCost[dar->storage];
+  return kPass * group_rows(dar, dar->dims.H, groups, clusters, !sums) <
+         c.pass_row * mega_slots(dar, dar->row_slots, dar->dims.H, days) + 0.14 * row_chain(dar);
+}
+
+bool group_cols_pay(const dode_dar* dar, int64_t groups, int64_t clusters, int64_t days) {
+  const FormCost& c = kCost[dar->storage];
+  const double chain = (dar->dims.P + 63) / 64 * dar->dims.K * ((dar->max_col + 7) / 8);
+  return kPass * group_cols(dar, dar->dims.T, groups, clusters, dar->dims.K, false) <
+         c.pass_col * mega_slots(dar, dar->col_slots, dar->dims.T, days) + c.pass_chain * chain;
+}
+
+bool group_step_pays(const dode_dar* dar, int32_t bh, int32_t touched, int64_t groups,
+                     int64_t clusters, int64_t days) {
+  const FormCost& c = kCost[dar->storage];
+  const double lags = (double)dar->dims.K * bh / std::max(1, touched);   // per reached interval
+  return group_rows(dar, bh, groups, clusters, true) + group_cols(dar, touched, groups, clusters, lags, true) <
+         c.step_row * mega_slots(dar, dar->row_slots, bh, days) + 0.07 * row_chain(dar) +
+             c.step_col * mega_slots(dar, dar->col_slots, bh, days) +
+             0.4 * lags * ((dar->max_col + 7) / 8) + 5.3;
 }
 
 hipError_t days_rows(const dode_dar* dar, const DayList& dl, const ChunkSched* cs, int32_t n_rows,

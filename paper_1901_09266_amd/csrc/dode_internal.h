@@ -116,7 +116,9 @@ struct dode_dar {
   int32_t* d_row = nullptr;
   int32_t* d_row_of_nz = nullptr; // link of CSR slot j
   int64_t sr_len = 0, sc_len = 0;   // sliced value layouts (see DevPat)
-  int32_t max_row = 0;              // most ODs of one link
+  int32_t max_row = 0, max_col = 0; // most ODs of one link, links of one OD
+  int64_t row_slots = 0, col_slots = 0;   // entries of a block in slices of 64 lines, by eight
+  int32_t value_size = 0;           // bytes of a stored value
   int32_t* d_sr_first = nullptr;   // sr_lane, then sr_first
   int32_t* d_sr_col = nullptr;
   int32_t* d_sr_pos = nullptr;
@@ -583,8 +585,17 @@ struct HostUnion {
 };
 HostUnion build_union(int32_t n_lines, int32_t n_cols, const std::vector<int32_t>& ptr,
                       const std::vector<int32_t>& idx, const std::vector<int32_t>& slot, bool f64);
-// days per group for clusters of up to n_days days: 1 = use the one-day kernels
-int32_t days_per_group(const dode_dar* dar, int32_t n_days);
+int32_t days_per_group();
+// whether the 16-day kernels can run: staged rows and launches over all groups
+bool day_groups_fit(const dode_dar* dar, int64_t groups);
+// whether they are estimated to be faster than one day per block, for `days` days
+// in `groups` groups of `clusters` clusters: whole passes of the product (sums: with
+// the rows' sums of squares) and of the adjoint, minibatches of bh rows that
+// reach `touched` intervals
+bool group_rows_pay(const dode_dar* dar, int64_t groups, int64_t clusters, int64_t days, bool sums);
+bool group_cols_pay(const dode_dar* dar, int64_t groups, int64_t clusters, int64_t days);
+bool group_step_pays(const dode_dar* dar, int32_t bh, int32_t touched, int64_t groups,
+                     int64_t clusters, int64_t days);
 // rows of cs (nullptr: every interval): out = rho Q (- X if X), in the R layout
 // for a minibatch and the X layout for whole days; part (nullable, whole days)
 // = [n][H] row sums of squares
