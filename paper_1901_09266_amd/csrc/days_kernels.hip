@@ -644,12 +644,17 @@ double mega_slots(const dode_dar* dar, int64_t slots, double n_rows, int64_t day
 
 }  // namespace
 
+bool day_launch_fits(int32_t n_rows, int64_t groups, int32_t n_tiles, bool rows) {
+  return (n_rows * groups + 7) / 8 * 8 * 64 * std::min(n_tiles, rows ? kRowWaves : kColWaves) <=
+         kGridThreads;
+}
+
 bool day_groups_fit(const dode_dar* dar, int64_t groups) {
   const size_t lines = std::max(dar->dims.P, dar->dims.L);
   const size_t rb = 16 * kDayTiles * (is_f64(dar) ? 8 : 4);
   // a staged row has to fit, and a launch of all groups
-  return lines * rb <= kLdsBytes &&
-         std::max(dar->dims.H, dar->dims.T) * groups * 16 <= INT32_MAX - 8;
+  return lines * rb <= kLdsBytes && day_launch_fits(dar->dims.H, groups, dar->u_rows.n_tiles, true) &&
+         day_launch_fits(dar->dims.T, groups, dar->u_cols.n_tiles, false);
 }
 
 int32_t days_per_group() { return 16 * kDayTiles; }

@@ -586,6 +586,9 @@ struct HostUnion {
 HostUnion build_union(int32_t n_lines, int32_t n_cols, const std::vector<int32_t>& ptr,
                       const std::vector<int32_t>& idx, const std::vector<int32_t>& slot, bool f64);
 int32_t days_per_group();
+// whether `groups` day groups of n_rows rows are one launch of a 16-day kernel
+// (rows: the forward, else the adjoint) whose lines make n_tiles tiles
+bool day_launch_fits(int32_t n_rows, int64_t groups, int32_t n_tiles, bool rows);
 // whether the 16-day kernels can run: staged rows and launches over all groups
 bool day_groups_fit(const dode_dar* dar, int64_t groups);
 // whether they are estimated to be faster than one day per block, for `days` days

@@ -31,3 +31,19 @@ def test_ratio_launches_stay_below_the_limit(L, f64, K, seg):
                 assert 0 <= n <= 16 and n * threads <= LIMIT
                 assert n == min(16, LIMIT // threads)   # and no smaller than it has to be
             assert fn(f64, n_paths, 16 * seg + 1, H, H, K) == 0   # two kernels
+
+
+@pytest.mark.parametrize("rows,waves", [(True, 8), (False, 16)])
+def test_launches_of_day_groups_stay_below_the_limit(L, rows, waves):
+    fn = L._Z15day_launch_fitsilib   # (n_rows, groups, n_tiles, rows)
+    fn.argtypes = [ctypes.c_int32, ctypes.c_int64, ctypes.c_int32, ctypes.c_bool]
+    fn.restype = ctypes.c_bool
+    for n_rows in (1, 7, 288, 1441, 65535):
+        for n_tiles in (1, 2, waves - 1, waves, waves + 1, 100):
+            threads = 64 * min(n_tiles, waves)
+            most = LIMIT // threads // 8 * 8 // n_rows   # grids are multiples of 8 blocks
+            for groups in (1, most - 1, most, most + 1, 2 * most, 2 ** 28):
+                if groups < 1:
+                    continue
+                blocks = (n_rows * groups + 7) // 8 * 8
+                assert fn(n_rows, groups, n_tiles, rows) == (blocks * threads <= LIMIT)
