@@ -504,16 +504,18 @@ __device__ __forceinline__ void put_four(double* p, const Four<double>& x, int v
     if (k < valid) p[k] = x.v[k];
 }
 
-// IN: caller to plan (with `clamp` projected onto >= 0), else plan to caller
+// Rows r0 .. r0+n_rows-1 of `rows`.  IN: caller to plan (with `clamp` projected onto
+// >= 0), else plan to caller
 template <typename S, bool IN>
 __global__ void __launch_bounds__(256)
 k_copy_days(const S* __restrict__ src, S* __restrict__ dst, const int32_t* __restrict__ order,
-            int32_t D, int32_t rows, int32_t n, int64_t sd, int64_t sr, int64_t sb, int clamp) {
+            int32_t D, int32_t rows, int32_t r0, int32_t n_rows, int32_t n, int64_t sd, int64_t sr,
+            int64_t sb, int clamp) {
   const int tiles = (D + kCopyDays - 1) / kCopyDays;
-  const int64_t n_blocks = (int64_t)rows * tiles, per = (n_blocks + 7) / 8;
+  const int64_t n_blocks = (int64_t)n_rows * tiles, per = (n_blocks + 7) / 8;
   const int64_t b = (blockIdx.x % 8) * per + blockIdx.x / 8;
   if (b >= n_blocks || blockIdx.x / 8 >= per) return;
-  const int r = (int)(b / tiles), tile = (int)(b - (int64_t)r * tiles);
+  const int row = (int)(b / tiles), r = r0 + row, tile = (int)(b - (int64_t)row * tiles);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int i = tile * kCopyDays + wave * 8 + (lane & 7);
   if (i >= D) return;
@@ -541,12 +543,17 @@ k_copy_days(const S* __restrict__ src, S* __restrict__ dst, const int32_t* __res
 template <typename S, bool IN>
 hipError_t copy_days(const void* src, void* dst, const int32_t* order, int32_t D, int32_t rows,
                      int32_t n, int64_t sd, int64_t sr, int64_t sb, bool clamp, hipStream_t s) {
-  const int64_t blocks = (int64_t)rows * ((D + kCopyDays - 1) / kCopyDays);
-  if (blocks > INT32_MAX - 8) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_copy_days<S, IN>), dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(256), 0, s,
-                     static_cast<const S*>(src), static_cast<S*>(dst), order, D, rows, n, sd, sr, sb,
-                     (int)clamp);
-  return hipGetLastError();
+  const int64_t tiles = (D + kCopyDays - 1) / kCopyDays;
+  const int64_t most = (kGridThreads / 256 - 7) / tiles;   // rows of a launch
+  if (most < 1) return hipErrorInvalidValue;
+  for (int64_t r0 = 0; r0 < rows; r0 += most) {
+    const int64_t nr = std::min<int64_t>(most, rows - r0);
+    hipLaunchKernelGGL((k_copy_days<S, IN>), dim3((unsigned)((nr * tiles + 7) / 8 * 8)), dim3(256), 0, s,
+                       static_cast<const S*>(src), static_cast<S*>(dst), order, D, rows, (int32_t)r0,
+                       (int32_t)nr, n, sd, sr, sb, (int)clamp);
+    if (const hipError_t e = hipGetLastError()) return e;
+  }
+  return hipSuccess;
 }
 
 template <typename S>

@@ -32,3 +32,21 @@ def test_ratios_of_more_patterns_than_a_launch_can_take():
         torch.cuda.synchronize()
         assert torch.equal(Rr[q], Rq) and torch.equal(cost[q], cq)
         assert (cost[q] > 0).all() and (Rr[q] >= 0).all()
+
+
+def test_state_copies_of_more_days_and_rows_than_a_launch_can_take():
+    """65,535 days of 8,200 intervals (blocks of 32 days of one row, 256 threads):
+    loaded into a plan and stored back, the demand is the same."""
+    D, T, P, L = 65_535, 8_200, 1, 2
+    say("copy launch limit", D, T)
+    dar = dode.dar_create(P, L, T, T, 1, np.array([0, 1, 1], np.int32), np.zeros(1, np.int32),
+                          np.ones((1, 1, T, 1)), storage="f32")
+    p = dode.make_params(epochs=1, batch_rows=T * L, kernel_path=1)
+    plan = dode.spgd_plan_create(dar, np.zeros(D, np.int32), p, seed=1)
+    X = torch.zeros((D, T, L), device="cuda")
+    Q = torch.arange(D * T, device="cuda", dtype=torch.float32).reshape(D, T, P)
+    out = torch.empty_like(Q)
+    dode.spgd_plan_load(plan, X, Q)
+    dode.spgd_plan_store(plan, out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, Q)
