@@ -158,6 +158,15 @@ void dode_spgd_defaults(dode_spgd_params* p);
  *   out             receives the handle; release it with dar_destroy
  * Errors: DODE_ERR_SHAPE for a malformed pattern, DODE_ERR_NONFINITE for
  * non-finite values, DODE_ERR_OOM, DODE_ERR_HIP.  Synchronises `stream`.
+ *
+ * Device memory (dar_info): two copies of the values, by link and by OD in slices
+ * of 64 lines as long as the longest of each, for BF16 and FP8 the matrix-core
+ * tiles, and, where kernels of 16 days per block can be of use (at most 64
+ * clusters, 16 days of a row of links or ODs fit into 156 KB), two more padded to
+ * tiles of 16 lines: 2 to 4 times the values where neighbouring lines share most
+ * of their entries, up to 13 times for independent incidence.  These last two are
+ * left out where they would take more than 16 GiB or a fourth of the memory that
+ * is free; the one-day kernels then serve every call.
  */
 dode_status dar_create(const dode_dims* dims, int32_t n_clusters, const int32_t* row_ptr,
                        const int32_t* col_idx, const double* const* values, dode_dtype storage,

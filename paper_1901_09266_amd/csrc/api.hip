@@ -20,7 +20,11 @@ namespace {
 
 // clusters of at most this many days use the sparse kernels under kernel_path 0
 constexpr int32_t kSparseDays = 2;
-// handles with packed union tiles: at most this many clusters and bytes
+// Handles with packed union tiles: at most this many clusters (more are taken for
+// single days, which the one-day kernels serve; up to here a handle of single days
+// carries them too, for passes over other days), and packed values of at most
+// this many bytes and a fourth of the memory that is free beside the rest of the
+// handle, which leaves plans theirs.
 constexpr int32_t kUnionClusters = 64;
 constexpr size_t kUnionBytes = size_t(16) << 30;
 
@@ -1152,33 +1156,6 @@ dode_status dar_create_ex(const dode_dims* dims, int32_t n_clusters, const int32
   }
 
   const size_t esz = d->value_size = storage == DODE_F64 ? 8 : storage == DODE_F32 ? 4 : storage == DODE_BF16 ? 2 : 1;
-  // union tiles and their packed values, for handles whose clusters hold
-  // several days (with more clusters they are single days, and those handles
-  // fill the memory); where they do not fit, the one-day kernels serve alone
-  HostUnion ur, uc;
-  if (nnz > 0 && n_clusters <= kUnionClusters) {
-    std::vector<int32_t> csc_slot(nnz);   // W slot of each CSC entry
-    for (int64_t jj = 0; jj < nnz; ++jj) csc_slot[jj] = sr_pos[d->h_csc2csr[jj]];
-    ur = build_union(dm.L, dm.P, d->h_row_ptr, d->h_col, sr_pos, storage == DODE_F64);
-    uc = build_union(dm.P, dm.L, d->h_col_ptr, d->h_row, csc_slot, storage == DODE_F64);
-    const size_t block = (size_t)n_clusters * dm.K * dm.T * esz;
-    const size_t rb = block * ur.code_of.size(), cb = block * uc.code_of.size();
-    if (rb + cb <= kUnionBytes) {
-      if (hipMalloc(&d->d_PR, rb) == hipSuccess && hipMalloc(&d->d_PC, cb) == hipSuccess) {
-        HIP_TRY(dev_copy(&d->d_u_rows, ur.buf));
-        HIP_TRY(dev_copy(&d->d_u_cols, uc.buf));
-        d->u_rows = ur.at(d->d_u_rows);
-        d->u_cols = uc.at(d->d_u_cols);
-        d->pr_len = (int64_t)ur.code_of.size();
-        d->pc_len = (int64_t)uc.code_of.size();
-        d->device_bytes += rb + cb;
-      } else {
-        if (d->d_PR) (void)hipFree(d->d_PR);
-        d->d_PR = nullptr;
-        (void)hipGetLastError();
-      }
-    }
-  }
   const int64_t cstride_r = (int64_t)dm.K * dm.T * d->sr_len, cstride_c = (int64_t)dm.K * dm.T * d->sc_len;
   const size_t vbytes_r = (size_t)n_clusters * cstride_r * esz, vbytes_c = (size_t)n_clusters * cstride_c * esz;
   HIP_TRY(hipMalloc(&d->d_W, std::max<size_t>(16, vbytes_r)));
@@ -1196,6 +1173,38 @@ dode_status dar_create_ex(const dode_dims* dims, int32_t n_clusters, const int32
     if (dode_status st = tiles_prepare(d.get(), err)) {
       dar_destroy(d.release());
       return fail(st, "tile layout: %s", err.c_str());
+    }
+  }
+  // union tiles and their packed values, after everything that the handle has to
+  // have; without them the one-day kernels serve alone
+  HostUnion ur, uc;
+  if (nnz > 0 && n_clusters <= kUnionClusters && day_rows_fit(d.get())) {
+    std::vector<int32_t> csc_slot(nnz);   // W slot of each CSC entry
+    for (int64_t jj = 0; jj < nnz; ++jj) csc_slot[jj] = sr_pos[d->h_csc2csr[jj]];
+    ur = build_union(dm.L, dm.P, d->h_row_ptr, d->h_col, sr_pos, storage == DODE_F64);
+    uc = build_union(dm.P, dm.L, d->h_col_ptr, d->h_row, csc_slot, storage == DODE_F64);
+    const size_t block = (size_t)n_clusters * dm.K * dm.T * esz;
+    const size_t rb = block * ur.code_of.size(), cb = block * uc.code_of.size();
+    size_t free_bytes = 0, all_bytes = 0;
+    HIP_TRY(hipMemGetInfo(&free_bytes, &all_bytes));
+    if (rb + cb <= std::min(kUnionBytes, free_bytes / 4)) {
+      d->u_rows.n_tiles = ur.n_tiles;
+      d->u_cols.n_tiles = uc.n_tiles;
+      d->pr_len = (int64_t)ur.code_of.size();
+      d->pc_len = (int64_t)uc.code_of.size();
+      if (groups_ever_pay(d.get())) {
+        if (hipMalloc(&d->d_PR, rb) == hipSuccess && hipMalloc(&d->d_PC, cb) == hipSuccess) {
+          HIP_TRY(dev_copy(&d->d_u_rows, ur.buf));
+          HIP_TRY(dev_copy(&d->d_u_cols, uc.buf));
+          d->u_rows = ur.at(d->d_u_rows);
+          d->u_cols = uc.at(d->d_u_cols);
+          d->device_bytes += rb + cb;
+        } else {
+          if (d->d_PR) (void)hipFree(d->d_PR);
+          d->d_PR = nullptr;
+          (void)hipGetLastError();
+        }
+      }
     }
   }
   {

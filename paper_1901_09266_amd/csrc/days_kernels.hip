@@ -649,11 +649,13 @@ bool day_launch_fits(int32_t n_rows, int64_t groups, int32_t n_tiles, bool rows)
          kGridThreads;
 }
 
-bool day_groups_fit(const dode_dar* dar, int64_t groups) {
+bool day_rows_fit(const dode_dar* dar) {
   const size_t lines = std::max(dar->dims.P, dar->dims.L);
-  const size_t rb = 16 * kDayTiles * (is_f64(dar) ? 8 : 4);
-  // a staged row has to fit, and a launch of all groups
-  return lines * rb <= kLdsBytes && day_launch_fits(dar->dims.H, groups, dar->u_rows.n_tiles, true) &&
+  return lines * 16 * kDayTiles * (is_f64(dar) ? 8 : 4) <= kLdsBytes;
+}
+
+bool day_groups_fit(const dode_dar* dar, int64_t groups) {
+  return day_rows_fit(dar) && day_launch_fits(dar->dims.H, groups, dar->u_rows.n_tiles, true) &&
          day_launch_fits(dar->dims.T, groups, dar->u_cols.n_tiles, false);
 }
 
@@ -680,6 +682,13 @@ bool group_step_pays(const dode_dar* dar, int32_t bh, int32_t touched, int64_t g
          c.step_row * mega_slots(dar, dar->row_slots, bh, days) + 0.07 * row_chain(dar) +
              c.step_col * mega_slots(dar, dar->col_slots, bh, days) +
              0.4 * lags * ((dar->max_col + 7) / 8) + 5.3;
+}
+
+bool groups_ever_pay(const dode_dar* dar) {
+  const int64_t groups = 256, days = groups * days_per_group();
+  return group_rows_pay(dar, groups, 1, days, true) || group_rows_pay(dar, groups, 1, days, false) ||
+         group_cols_pay(dar, groups, 1, days) ||
+         group_step_pays(dar, dar->dims.H, dar->dims.T, groups, 1, days);
 }
 
 hipError_t days_rows(const dode_dar* dar, const DayList& dl, const ChunkSched* cs, int32_t n_rows,

@@ -589,7 +589,9 @@ int32_t days_per_group();
 // whether `groups` day groups of n_rows rows are one launch of a 16-day kernel
 // (rows: the forward, else the adjoint) whose lines make n_tiles tiles
 bool day_launch_fits(int32_t n_rows, int64_t groups, int32_t n_tiles, bool rows);
-// whether the 16-day kernels can run: staged rows and launches over all groups
+// whether a block can stage a row of 16 days, and then whether the 16-day kernels
+// can run: launches over all groups
+bool day_rows_fit(const dode_dar* dar);
 bool day_groups_fit(const dode_dar* dar, int64_t groups);
 // whether they are estimated to be faster than one day per block, for `days` days
 // in `groups` groups of `clusters` clusters: whole passes of the product (sums: with
@@ -599,6 +601,8 @@ bool group_rows_pay(const dode_dar* dar, int64_t groups, int64_t clusters, int64
 bool group_cols_pay(const dode_dar* dar, int64_t groups, int64_t clusters, int64_t days);
 bool group_step_pays(const dode_dar* dar, int32_t bh, int32_t touched, int64_t groups,
                      int64_t clusters, int64_t days);
+// whether any of these is so for thousands of days
+bool groups_ever_pay(const dode_dar* dar);
 // rows of cs (nullptr: every interval): out = rho Q (- X if X), in the R layout
 // for a minibatch and the X layout for whole days; part (nullable, whole days)
 // = [n][H] row sums of squares
