@@ -61,7 +61,7 @@ k_install(DevPat pt, DevTiles tl, int32_t c, const S* __restrict__ src,
           DevVals dv, float* __restrict__ scale, const int32_t* __restrict__ code_of) {
   using E = typename CodeT<ST>::E;
   extern __shared__ __align__(16) unsigned char stage_mem[];
-  const int lt = blockIdx.x, tid = threadIdx.x;
+  const int lt = blockIdx.y * pt.T + blockIdx.x, tid = threadIdx.x;
   const int64_t blk = (int64_t)c * pt.K * pt.T + lt;
   const int n_ptile = dv.n_ptile;
   E* wb = static_cast<E*>(const_cast<void*>(dv.W)) + blk * pt.sr_len;
@@ -117,7 +117,7 @@ k_install(DevPat pt, DevTiles tl, int32_t c, const S* __restrict__ src,
     idx += len / 4;
   };
   fill(dv.WT, pt.sc_len);
-  if (lt / pt.T + lt % pt.T >= pt.H) return;   // a block no product reads
+  if (blockIdx.y + blockIdx.x >= (unsigned)pt.H) return;   // a block no product reads
   if (dv.PR) {
     fill(dv.PR, dv.pr_len);
     fill(dv.PC, dv.pc_len);
@@ -134,7 +134,7 @@ hipError_t launch(const dode_dar* dar, int32_t c, const void* src, hipStream_t s
   const size_t stage = (size_t)dar->sr_len * sizeof(E);
   const bool fits = stage <= kStageBytes;
   auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3(dar->dims.K * dar->dims.T), dim3(kBlock), fits ? stage : 0, s,
+    hipLaunchKernelGGL(kern, dim3(dar->dims.T, dar->dims.K), dim3(kBlock), fits ? stage : 0, s,
                        dar->pat(), dar->tiles, c, static_cast<const S*>(src), dar->vals(),
                        dar->d_scale, dar->d_code_of);
   };

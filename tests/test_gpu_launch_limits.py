@@ -50,3 +50,18 @@ def test_state_copies_of_more_days_and_rows_than_a_launch_can_take():
     dode.spgd_plan_store(plan, out)
     torch.cuda.synchronize()
     assert torch.equal(out, Q)
+
+
+def test_handle_of_more_blocks_than_a_launch_can_take():
+    """Two lags of 4.2 M intervals: 8.4 M blocks of 512 threads install the values."""
+    T, K = 4_200_000, 2
+    say("install launch limit", T, K)
+    W = np.ones((1, K, T, 1))
+    W[0, 1] = 2.0
+    dar = dode.dar_create(1, 1, T, T, K, np.array([0, 1], np.int32), np.zeros(1, np.int32), W,
+                          storage="bf16")
+    Q = torch.arange(T, device="cuda", dtype=torch.float32).remainder(1024).reshape(1, T, 1)
+    X = torch.empty_like(Q)
+    dode.dode_apply(dar, 0, Q, X)
+    torch.cuda.synchronize()
+    assert torch.equal(X[0, 0], Q[0, 0]) and torch.equal(X[0, 1:], Q[0, 1:] + 2 * Q[0, :-1])
