@@ -63,30 +63,6 @@ struct Vec<double> {
   }
 };
 
-// Values as they are stored.
-template <int ST>
-struct Stored;
-template <>
-struct Stored<DODE_F64> {
-  using T = double;
-  __device__ static double widen(T r) { return r; }
-};
-template <>
-struct Stored<DODE_F32> {
-  using T = float;
-  __device__ static float widen(T r) { return r; }
-};
-template <>
-struct Stored<DODE_BF16> {
-  using T = uint16_t;
-  __device__ static float widen(T r) { return bf16_bits_to_f32(r); }
-};
-template <>
-struct Stored<DODE_FP8_E4M3> {   // the scale is applied by the caller
-  using T = uint8_t;
-  __device__ static float widen(T r) { return e4m3_bits_to_f32(r); }
-};
-
 // Cluster, first day and day count of group g.
 template <int ND>
 __device__ __forceinline__ void day_group(const DayList& dl, int g, int& c, int& first, int& cnt) {
@@ -188,7 +164,7 @@ template <int ST, typename S, int NT, typename B, typename F>
 __device__ __forceinline__ void tile_product(const DevUnion& un, int tile, int n_lags, int n_cols,
                                              const S* st, const void* vals, int64_t len, B&& block,
                                              F&& scale, typename Vec<S>::V4* acc) {
-  using E = typename Stored<ST>::T;
+  using E = typename Load<ST>::E;
   struct alignas(4 * sizeof(E)) E4 {
     E v[4];
   };
@@ -228,7 +204,7 @@ __device__ __forceinline__ void tile_product(const DevUnion& un, int tile, int n
       for (int u = 0; u < NT; ++u) x[j][u] = row[at[j] * ND + 16 * u];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      S a = Stored<ST>::widen(q.w.v[j]);
+      S a = Load<ST>::raw(q.w.v[j]);
       if constexpr (ST == DODE_FP8_E4M3) a *= scale(block(q.i), at[j]);
       a = on ? a : S(0);
 #pragma unroll

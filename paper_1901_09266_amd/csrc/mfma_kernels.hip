@@ -1072,15 +1072,16 @@ hipError_t launch_fwd(const dode_dar* dar, const ChunkSched& cs, const WaveWork*
   // times as fast, below 0.94 to 1.02).
   const bool pays = MODE == kFP8 ? dar->dims.K * (int64_t)dar->tiles.kf_total >= 4 * dar->tiles.nLT
                                  : n >= 768 * kFwdWaves;
-  if (pays && mfma_fwd_shares(dar, 16 * NT, MODE == kFP8Corr)) {
-    const int64_t lag_bytes = fwd_lag_bytes(dar, 16 * NT);
-    const int lags = (int)std::max<int64_t>(1, std::min<int64_t>(dar->dims.K, kFwdStage / lag_bytes));
-    const int64_t nblk = n / kFwdWaves;
-    const dim3 grid((unsigned)(((nblk + kXcds - 1) / kXcds) * kXcds));
-    hipLaunchKernelGGL((k_fwd_block<MODE, NT>), grid, dim3(kFwdBlock), lags * lag_bytes, s,
-                       dar->pat(), dar->tiles, cs, wt, (int)n, ly, lags, Q, X, R);
-    return hipGetLastError();
-  }
+  if constexpr (MODE != kFP8Corr || NT == 1)   // the others never share
+    if (pays && mfma_fwd_shares(dar, 16 * NT, MODE == kFP8Corr)) {
+      const int64_t lag_bytes = fwd_lag_bytes(dar, 16 * NT);
+      const int lags = (int)std::max<int64_t>(1, std::min<int64_t>(dar->dims.K, kFwdStage / lag_bytes));
+      const int64_t nblk = n / kFwdWaves;
+      const dim3 grid((unsigned)(((nblk + kXcds - 1) / kXcds) * kXcds));
+      hipLaunchKernelGGL((k_fwd_block<MODE, NT>), grid, dim3(kFwdBlock), lags * lag_bytes, s,
+                         dar->pat(), dar->tiles, cs, wt, (int)n, ly, lags, Q, X, R);
+      return hipGetLastError();
+    }
   const int64_t nblk = (n + 3) / 4;
   const dim3 grid((unsigned)(((nblk + kXcds - 1) / kXcds) * kXcds));
   hipLaunchKernelGGL((k_fwd_mfma<MODE, NT>), grid, dim3(256), 0, s, dar->pat(), dar->tiles, cs, wt,

@@ -20,13 +20,15 @@ __device__ __forceinline__ float e4m3_bits_to_f32(uint8_t b) {
 }
 
 // Stored values widened to the state type: one, or a neighbouring pair.
-// `scale` holds the FP8 scales of the value's block, one per 64 ODs.
+// `scale` holds the FP8 scales of the value's block, one per 64 ODs; raw leaves
+// the scale to the caller.
 template <int ST>
 struct Load;
 template <>
 struct Load<DODE_F64> {
   using E = double;
   using Pair = double2;
+  __device__ static double raw(double w) { return w; }
   __device__ static double widen(double w, const float*, int) { return w; }
   __device__ static void widen(double2 w, const float*, int2, double& w0, double& w1) {
     w0 = w.x;
@@ -37,6 +39,7 @@ template <>
 struct Load<DODE_F32> {
   using E = float;
   using Pair = float2;
+  __device__ static float raw(float w) { return w; }
   __device__ static float widen(float w, const float*, int) { return w; }
   __device__ static void widen(float2 w, const float*, int2, float& w0, float& w1) {
     w0 = w.x;
@@ -47,7 +50,8 @@ template <>
 struct Load<DODE_BF16> {
   using E = uint16_t;
   using Pair = uint32_t;
-  __device__ static float widen(uint16_t w, const float*, int) { return bf16_bits_to_f32(w); }
+  __device__ static float raw(uint16_t w) { return bf16_bits_to_f32(w); }
+  __device__ static float widen(uint16_t w, const float*, int) { return raw(w); }
   __device__ static void widen(uint32_t w, const float*, int2, float& w0, float& w1) {
     w0 = bf16_bits_to_f32(static_cast<uint16_t>(w & 0xFFFFu));
     w1 = bf16_bits_to_f32(static_cast<uint16_t>(w >> 16));
@@ -57,8 +61,9 @@ template <>
 struct Load<DODE_FP8_E4M3> {
   using E = uint8_t;
   using Pair = uint16_t;
+  __device__ static float raw(uint8_t w) { return e4m3_bits_to_f32(w); }
   __device__ static float widen(uint8_t w, const float* scale, int tile) {
-    return e4m3_bits_to_f32(w) * scale[tile];
+    return raw(w) * scale[tile];
   }
   __device__ static void widen(uint16_t w, const float* scale, int2 p, float& w0, float& w1) {
     w0 = e4m3_bits_to_f32(static_cast<uint8_t>(w & 0xFFu)) * scale[p.x >> 6];
