@@ -164,7 +164,7 @@ void dode_spgd_defaults(dode_spgd_params* p);
  * tiles, and, where kernels of 16 days per block can be of use (at most 64
  * clusters, 16 days of a row of links or ODs fit into 156 KB), two more padded to
  * tiles of 16 lines: 2 to 4 times the values where neighbouring lines share most
- * of their entries, up to 13 times for independent incidence.  These last two are
+ * of their entries, up to 15 times for independent incidence.  These last two are
  * left out where they would take more than 16 GiB or a fourth of the memory that
  * is free; the one-day kernels then serve every call.
  */

@@ -7,12 +7,15 @@
 // Tiles: 16 lines (links of the product, ODs of the adjoint) by the union of
 // the columns that any of them has an entry in, four columns a group, made
 // once per handle from the pattern (unions.hip).  The values are kept packed in
-// operand order (1.4 to 2 stored per entry on a corridor), so a column group is
-// one coalesced load; gathered from the sliced copies instead, the 64 values of
-// a group lie in up to 64 cache lines (ODs: 950 against 553 us of the
-// one-line-per-lane form below).  A block owns one row block (interval h, departure interval t) for
-// ND = 16 NT days: it stages the state rows its lags need in LDS, days fastest,
-// and its waves take the tiles in turn.
+// operand order, runs of 16 columns, so a column group is one coalesced load;
+// gathered from the sliced copies instead, the 64 values of a group lie in up to
+// 64 cache lines (ODs: 950 against 553 us of the one-line-per-lane form below).
+// Stored per entry, by link / by OD, with the padding of tiles and runs: corridor
+// 400 x 1500 8% 1.3 / 1.5, 150 x 500 8% 2.0 / 2.4, 50 x 200 10% 2.8 / 4.1;
+// independent incidence 150 x 500 8% 9.0 / 9.2, 3% 12.1 / 12.8.  A block owns one
+// row block (interval h, departure interval t) for ND = 16 NT days: it stages the
+// state rows its lags need in LDS, days fastest, and its waves take the tiles in
+// turn.
 //
 // v_mfma_f32_16x16x4_f32 adds its four products to the accumulator one after
 // the other, each with one rounding (fused multiply-add, increasing k), and a

@@ -643,9 +643,10 @@ hipError_t dar_from_speeds(bool f64, int32_t n_paths, const int32_t* path_ptr,
 // The same for several patterns in one kernel (pattern_ptr host
 // [n_patterns+1]; Rr [n_patterns][K][H][n_pairs], cost [n_patterns][H][n_paths]
 // or nullptr), the days of a pattern in n_parts parts, each with dar_part_bytes of
-// `parts` (unused with one); dar_parts: how many (more than one for calls of few
-// blocks), 0 where the two kernels are faster; traj_bytes: their trajectories; dar_fused_patterns: the patterns of one launch, 0 where paths of
-// up to `longest` links, or a launch of one pattern, do not fit it
+// `parts` (unused with one).  dar_parts: how many (more than one for calls of few
+// blocks), 0 where the two kernels are faster (traj_bytes: their trajectories);
+// dar_fused_patterns: the patterns of one launch, 0 where paths of up to `longest`
+// links, or a launch of one pattern, do not fit it
 int32_t dar_fused_patterns(bool f64, int32_t n_paths, int32_t longest, int32_t H, int32_t H_speed,
                            int32_t K);
 int32_t dar_parts(bool f64, int32_t n_paths, int32_t longest, int32_t H, int32_t K,
