@@ -340,7 +340,7 @@ dode_status dar_logits_bwd(const dode_routes* routes, int32_t f64, const void* R
  * Errors: DODE_ERR_SHAPE for malformed path tables, DODE_ERR_ARG for
  * non-positive or non-finite lengths or speeds.  Synchronises `stream` (the
  * path tables and the checks are read back).  Calls with paths of more than 128
- * links (64 with K > 8; half of that with f64), or of few long paths, use a
+ * links (64 with K > 8; half of that with f64), or of few paths and days, use a
  * scratch buffer of at most 4 GiB (the trajectories of a chunk of days), or of
  * the byte count in the environment variable DODE_DAR_SCRATCH_BYTES (smaller
  * values process fewer days at a time; a value that is not a positive integer is

@@ -1611,16 +1611,13 @@ dode_status dode_dar_patterns_from_speeds(int32_t n_paths, const int32_t* path_p
   }
   int32_t most = 0;
   for (int32_t q = 0; q < n_patterns; ++q) most = std::max(most, pattern_ptr[q + 1] - pattern_ptr[q]);
-  const size_t part = dar_part_bytes(f64 != 0, n_paths, n_pairs, H, K, n_patterns);
-  int32_t n_parts = 0;
-  if (dar_fused_patterns(f64 != 0, n_paths, longest, H, H_speed, K) > 0)
-    n_parts = dar_parts(f64 != 0, n_paths, longest, H, K, n_patterns, most, part, per_day * most);
-  if (n_parts > 0) {   // no trajectories, at most the sums of the parts
-    if (part * n_parts > limit) n_parts = 1;
-    DevBuf parts;
-    if (n_parts > 1) HIP_TRY(parts.alloc(part * n_parts, s));
+  const DarSplit split =
+      dar_split(f64 != 0, n_paths, n_pairs, longest, H, H_speed, K, n_patterns, pattern_ptr, limit);
+  if (split.per_launch > 0) {   // no trajectories
+    DevBuf sums;
+    if (split.scratch) HIP_TRY(sums.alloc(split.scratch, s));
     HIP_TRY(dar_ratios(f64 != 0, n_paths, path_ptr, path_link, n_pairs, longest, L, link_len, speed,
-                       n_patterns, pattern_ptr, H_speed, dt, H, K, Rr, cost, n_parts, parts.p, s));
+                       n_patterns, pattern_ptr, H_speed, dt, H, K, Rr, cost, split, sums.p, s));
     return DODE_OK;
   }
   const size_t cap = std::max<size_t>(1, limit / std::max<size_t>(per_day, 1));

@@ -211,8 +211,8 @@ k_dar_windows(int64_t n_pairs, int32_t n_days_chunk, int32_t H, int32_t K, S dt,
 // form a pipeline over the groups of days, one step per barrier.  The speed
 // gathers of a link are in flight while its windows are added.  Days are added
 // in order, so the results are those of the two kernels above for any grouping.
-// Where the blocks are too few to fill the chip (ratio_parts), the days of a
-// pattern are split over gridDim.y parts, whose sums k_join_parts adds in order.
+// Where a pattern's blocks are too few to fill the chip (dar_split), its days are
+// split over parts (blockIdx.y), whose sums k_join_parts adds in order.
 //
 // What bounds it: the VALU (about 45 instructions per day, link and boundary
 // in FP32) and the chain of gathers along a path.  The trajectories of the two
@@ -224,6 +224,7 @@ constexpr int kMaxSegs = 16;   // waves of a block
 constexpr int kPatterns = 16;  // patterns of one launch
 struct PatternDays {
   int32_t ptr[kPatterns + 1];
+  int32_t parts[kPatterns];
 };
 
 // RN(t / dt) with rdt = RN(1 / dt): two residual steps on the approximate
@@ -259,8 +260,9 @@ k_ratios(int32_t n_paths, const int32_t* __restrict__ path_ptr,
   item /= n_chunks;
   const int k = item % n_paths, q = item / n_paths;
   // the block's days: whole groups, a part of the pattern's
-  const int all = days.ptr[q + 1] - days.ptr[q];
-  const int per = ((all + ND - 1) / ND + gridDim.y - 1) / gridDim.y * ND;
+  const int all = days.ptr[q + 1] - days.ptr[q], n_parts = days.parts[q];
+  if ((int)blockIdx.y >= n_parts) return;
+  const int per = ((all + ND - 1) / ND + n_parts - 1) / n_parts * ND;
   const int skip = min(all, (int)blockIdx.y * per);
   const int d_begin = days.ptr[q] + skip, n_days = min(per, all - skip);
   const int m0 = path_ptr[k], m_end = path_ptr[k + 1];
@@ -352,7 +354,7 @@ k_ratios(int32_t n_paths, const int32_t* __restrict__ path_ptr,
   }
   const int h = chunk * kWin + lane;   // the lane's interval
   if (lane == kWin || h >= H) return;
-  if (gridDim.y > 1) {
+  if (n_parts > 1) {
     const int64_t row = (int64_t)blockIdx.y * (gridDim.x / (n_paths * n_chunks)) + q;
     if (wave == n_segs - 1) part_exit[(row * H + h) * n_paths + k] = exit_sum;
 #pragma unroll
@@ -379,14 +381,16 @@ k_ratios(int32_t n_paths, const int32_t* __restrict__ path_ptr,
   }
 }
 
-// Means over the days of pattern blockIdx.y from the sums of its parts: ratios
-// (idx below K*H*n_pairs), then path costs.
+// Means over the days of pattern blockIdx.y from the sums of its parts, if it has
+// several: ratios (idx below K*H*n_pairs), then path costs.
 template <typename S>
 __global__ void __launch_bounds__(kBlock)
-k_join_parts(int32_t n_parts, PatternDays days, int32_t n_paths, int64_t n_pairs, int32_t H, int32_t K,
+k_join_parts(PatternDays days, int32_t n_paths, int64_t n_pairs, int32_t H, int32_t K,
              const double* __restrict__ part_exit, const S* __restrict__ part_sum,
              S* __restrict__ Rr, S* __restrict__ cost) {
   const int q = blockIdx.y, nq = gridDim.y, n_days = days.ptr[q + 1] - days.ptr[q];
+  const int n_parts = days.parts[q];
+  if (n_parts == 1) return;
   const int64_t n_r = (int64_t)K * H * n_pairs, n_c = (int64_t)H * n_paths;
   int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i < n_r) {
@@ -507,30 +511,33 @@ template <typename S, int KMAX>
 hipError_t run_fused(int32_t n_paths, const int32_t* path_ptr, const int32_t* path_link,
                      int64_t n_pairs, int32_t longest, int32_t L, const S* len, const S* speed,
                      int32_t n_patterns, const int32_t* pattern_ptr, int32_t H_speed, S dt,
-                     int32_t H, int32_t K, S* Rr, S* cost, int32_t n_parts, void* parts,
+                     int32_t H, int32_t K, S* Rr, S* cost, const DarSplit& split, void* scratch,
                      hipStream_t s) {
   constexpr int SEG = Seg<S, KMAX>::kLinks, ND = Seg<S, KMAX>::kDays;
   const int nw = std::max(1, (longest + SEG - 1) / SEG);
   const int64_t per = (int64_t)n_paths * ((H + 62) / 63);
   const size_t lds = (size_t)2 * nw * ND * 64 * sizeof(S);
-  const int32_t per_launch =
-      dar_fused_patterns(sizeof(S) == 8, n_paths, longest, H, H_speed, K);
-  if (per_launch < 1) return hipErrorInvalidValue;
-  for (int32_t q0 = 0; q0 < n_patterns; q0 += per_launch) {
-    const int32_t nq = std::min(per_launch, n_patterns - q0);
+  if (split.per_launch < 1) return hipErrorInvalidValue;
+  for (int32_t q0 = 0; q0 < n_patterns; q0 += split.per_launch) {
+    const int32_t nq = std::min(split.per_launch, n_patterns - q0);
     PatternDays pd{};
-    for (int32_t q = 0; q <= nq; ++q) pd.ptr[q] = pattern_ptr[q0 + q];
-    double* exits = static_cast<double*>(parts);
-    S* sums = reinterpret_cast<S*>(exits + (int64_t)n_parts * nq * H * n_paths);
+    int32_t most = 1;   // parts of a pattern
+    pd.ptr[0] = pattern_ptr[q0];
+    for (int32_t q = 0; q < nq; ++q) {
+      pd.ptr[q + 1] = pattern_ptr[q0 + q + 1];
+      most = std::max(most, pd.parts[q] = split.parts[q0 + q]);
+    }
+    double* exits = static_cast<double*>(scratch);
+    S* sums = reinterpret_cast<S*>(exits + (int64_t)most * nq * H * n_paths);
     S* rq = Rr + (int64_t)q0 * K * H * n_pairs;
     S* cq = cost ? cost + (int64_t)q0 * H * n_paths : nullptr;
-    hipLaunchKernelGGL((k_ratios<S, KMAX, SEG, ND>), dim3((unsigned)(per * nq), n_parts), dim3(64 * nw),
+    hipLaunchKernelGGL((k_ratios<S, KMAX, SEG, ND>), dim3((unsigned)(per * nq), most), dim3(64 * nw),
                        lds, s, n_paths, path_ptr, path_link, L, len, speed, pd, H_speed, dt,
                        static_cast<S>(1) / dt, H, K, n_pairs, rq, cq, exits, sums);
-    if (n_parts > 1)
+    if (most > 1)
       hipLaunchKernelGGL(k_join_parts<S>,
                          dim3(blocks_for((int64_t)K * H * n_pairs + (int64_t)H * n_paths), nq),
-                         dim3(kBlock), 0, s, n_parts, pd, n_paths, n_pairs, H, K, exits, sums, rq, cq);
+                         dim3(kBlock), 0, s, pd, n_paths, n_pairs, H, K, exits, sums, rq, cq);
   }
   return hipGetLastError();
 }
@@ -539,13 +546,13 @@ template <typename S>
 hipError_t fused(int32_t n_paths, const int32_t* path_ptr, const int32_t* path_link,
                  int64_t n_pairs, int32_t longest, int32_t L, const void* len, const void* speed,
                  int32_t n_patterns, const int32_t* pattern_ptr, int32_t H_speed, double dt,
-                 int32_t H, int32_t K, void* Rr, void* cost, int32_t n_parts, void* parts,
+                 int32_t H, int32_t K, void* Rr, void* cost, const DarSplit& split, void* scratch,
                  hipStream_t s) {
   auto go = [&](auto kmax) {
     return run_fused<S, decltype(kmax)::value>(
         n_paths, path_ptr, path_link, n_pairs, longest, L, static_cast<const S*>(len),
         static_cast<const S*>(speed), n_patterns, pattern_ptr, H_speed, static_cast<S>(dt), H, K,
-        static_cast<S*>(Rr), static_cast<S*>(cost), n_parts, parts, s);
+        static_cast<S*>(Rr), static_cast<S*>(cost), split, scratch, s);
   };
   if (K <= 3) return go(std::integral_constant<int, 3>{});
   if (K <= 6) return go(std::integral_constant<int, 6>{});
@@ -620,45 +627,76 @@ int32_t dar_fused_patterns(bool f64, int32_t n_paths, int32_t longest, int32_t H
   return (int32_t)std::min<int64_t>(kPatterns, kGridThreads / threads);
 }
 
-size_t dar_part_bytes(bool f64, int32_t n_paths, int64_t n_pairs, int32_t H, int32_t K,
-                      int32_t n_patterns) {
-  return (size_t)std::min(n_patterns, kPatterns) * H *
-         ((size_t)K * n_pairs * (f64 ? 8 : 4) + (size_t)n_paths * 8);
-}
-
-int32_t dar_parts(bool f64, int32_t n_paths, int32_t longest, int32_t H, int32_t K,
-                  int32_t n_patterns, int32_t most_days, size_t part_bytes, size_t traj_bytes) {
-  // A block takes the days of its pattern one group after the other, 5 to 13 us a
-  // group, and a group passes through a segment of links after the other.  Up to
-  // a block per CU the groups are split for two blocks per CU, at least four
-  // groups to a part, where that saves more than the parts cost (whole calls with
-  // the splits, without, and in the two kernels; 20 links, 288 intervals, FP32:
-  // 365 days, 1 path 198, 713 and 332 us, 10 paths 273, 718 and 647, 30 paths 419,
-  // 721 and 677, 50 paths 522, 721 and 816; 1095 days, 10 paths 442, 1934 and 1122).
+DarSplit dar_split(bool f64, int32_t n_paths, int64_t n_pairs, int32_t longest, int32_t H,
+                   int32_t H_speed, int32_t K, int32_t n_patterns, const int32_t* pattern_ptr,
+                   size_t limit) {
+  DarSplit sp;
+  sp.per_launch = dar_fused_patterns(f64, n_paths, longest, H, H_speed, K);
+  if (sp.per_launch < 1) return sp;
   const int seg = f64 ? (K <= 8 ? Seg<double, 8>::kLinks : Seg<double, 16>::kLinks)
                       : (K <= 8 ? Seg<float, 8>::kLinks : Seg<float, 16>::kLinks);
   const int nd = f64 ? (K <= 8 ? Seg<double, 8>::kDays : Seg<double, 16>::kDays) : Seg<float, 8>::kDays;
-  const int64_t blocks = (int64_t)n_paths * (((int64_t)H + 62) / 63) * std::min(n_patterns, kPatterns);
-  const int64_t groups = ((int64_t)most_days + nd - 1) / nd;
-  if (blocks > 256) return 1;
-  int64_t parts = std::max<int64_t>(1, std::min(512 / blocks, groups / 4));
-  parts = std::min(parts, std::max<int64_t>(1, (int64_t)((size_t(64) << 20) / part_bytes)));
-  const double saved = (groups - (groups + parts - 1) / parts) * (2.0 + 1.4 * std::min(longest, seg));
-  if (saved < 50.0 + 6e-6 * part_bytes * parts) parts = 1;   // us: sums, launch, allocation
-  // Few days of long paths are mostly segments; the two kernels take links side
-  // by side, but the patterns in turn, and trajectories have to be allocated.
-  const int64_t segs = (longest + seg - 1) / seg - 1, steps = (groups + parts - 1) / parts + segs;
-  if (blocks <= 128 && segs >= 8 && steps >= 15 * (int64_t)n_patterns && traj_bytes <= (size_t(64) << 20)) return 0;
-  return (int32_t)parts;
+  const size_t ss = f64 ? 8 : 4;
+  const int64_t blocks = (int64_t)n_paths * (((int64_t)H + 62) / 63);   // of a pattern
+  const int64_t segs = std::max(1, (longest + seg - 1) / seg) - 1;   // steps until the last one starts
+  const size_t part_bytes = (size_t)H * ((size_t)K * n_pairs * ss + (size_t)n_paths * 8);
+  limit = std::min(limit, size_t(64) << 20);
+  // A block takes the days of its pattern one group after the other, and a group
+  // passes through a segment of links after the other: us of a step, and of a call
+  // of `steps` whose blocks fit the chip together.
+  const double step_us = 1.5 * std::min(longest, seg) * (K > 8 ? 1.7 : 1.0);
+  auto one_us = [&](int64_t steps) { return 80.0 + step_us * steps; };
+  // The two kernels take links and days side by side, but the patterns in turn, and
+  // trajectories have to be allocated.  Both models within 10 and 21% (standard
+  // deviation) over 618 calls of 1 to 100 paths of 3 to 60 links, 8 to 1095 days in 1
+  // and 4 patterns (120 days of one path of 60 links, 24 intervals, 12 lags, FP32:
+  // 218 us in two kernels, 426 in one).
+  auto two_pay = [&](int64_t steps, int64_t patterns, int64_t all_days, int64_t most) {
+    const double mb = 1e-6 * n_pairs * (H + 1) * ss * most;
+    return blocks * patterns <= 128 && mb <= 64.0 &&
+           1.2 * (104.0 + 26.0 * patterns + (0.34 + 0.01 * longest) * all_days + 2.1 * mb) < one_us(steps);
+  };
+  // The groups of a pattern are split for two blocks per CU (one, if its segments make
+  // more than four waves) as long as a part has more groups than the blocks have
+  // segments to fill, and for up to 64 blocks down to four groups a part, where that
+  // saves more than the parts' sums cost (whole calls with the splits, without, and in
+  // the two kernels; 20 links, 288 intervals, FP32: 365 days, 1 path 207, 713 and 332
+  // us, 10 paths 264, 718 and 647, 30 paths 404, 721 and 677, 50 paths 513, 721 and 816;
+  // 1095 days, 10 paths 433, 1934 and 1122, in 4 patterns 374, 604 and 860).
+  // The parts follow from the pattern's own days alone, so that it has the same
+  // bits in a call of its own.
+  int32_t most_parts = 1, most_days = 0;
+  for (int32_t q = 0; q < n_patterns; ++q) {
+    const int64_t days = pattern_ptr[q + 1] - pattern_ptr[q], groups = (days + nd - 1) / nd;
+    int64_t parts = std::max(std::min(64 / blocks, groups / 4),
+                             std::min((segs < 4 ? 512 : 256) / blocks,
+                                      groups / std::max<int64_t>(4, segs)));
+    parts = std::max<int64_t>(1, std::min<int64_t>(parts, limit / part_bytes));
+    const int64_t steps = (groups + parts - 1) / parts;
+    if (step_us * (groups - steps) < 50.0 + 6e-6 * part_bytes * parts ||   // sums, launch, allocation
+        two_pay(steps + segs, 1, days, days))
+      parts = 1;
+    sp.parts.push_back((int32_t)parts);
+    most_parts = std::max(most_parts, (int32_t)parts);
+    most_days = std::max(most_days, (int32_t)days);
+  }
+  if (most_parts == 1) {
+    if (two_pay((most_days + nd - 1) / nd + segs, n_patterns, pattern_ptr[n_patterns], most_days))
+      sp.per_launch = 0;
+    return sp;
+  }
+  sp.per_launch = (int32_t)std::min<int64_t>(sp.per_launch, limit / (most_parts * part_bytes));
+  sp.scratch = std::min(sp.per_launch, n_patterns) * most_parts * part_bytes;
+  return sp;
 }
 
 hipError_t dar_ratios(bool f64, int32_t n_paths, const int32_t* path_ptr, const int32_t* path_link,
                       int64_t n_pairs, int32_t longest, int32_t L, const void* len,
                       const void* speed, int32_t n_patterns, const int32_t* pattern_ptr,
                       int32_t H_speed, double dt, int32_t H, int32_t K, void* Rr, void* cost,
-                      int32_t n_parts, void* parts, hipStream_t s) {
+                      const DarSplit& split, void* scratch, hipStream_t s) {
   return f64 ? fused<double>(n_paths, path_ptr, path_link, n_pairs, longest, L, len, speed,
-                             n_patterns, pattern_ptr, H_speed, dt, H, K, Rr, cost, n_parts, parts, s)
+                             n_patterns, pattern_ptr, H_speed, dt, H, K, Rr, cost, split, scratch, s)
              : fused<float>(n_paths, path_ptr, path_link, n_pairs, longest, L, len, speed,
-                            n_patterns, pattern_ptr, H_speed, dt, H, K, Rr, cost, n_parts, parts, s);
+                            n_patterns, pattern_ptr, H_speed, dt, H, K, Rr, cost, split, scratch, s);
 }

@@ -640,24 +640,28 @@ hipError_t dar_from_speeds(bool f64, int32_t n_paths, const int32_t* path_ptr,
                            const void* speed, int32_t n_days, int32_t H_speed, double dt, int32_t H,
                            int32_t K, void* traj, int32_t chunk, void* Rr, void* exit_time,
                            double* sums, void* cost, hipStream_t s);
-// The same for several patterns in one kernel (pattern_ptr host
-// [n_patterns+1]; Rr [n_patterns][K][H][n_pairs], cost [n_patterns][H][n_paths]
-// or nullptr), the days of a pattern in n_parts parts, each with dar_part_bytes of
-// `parts` (unused with one).  dar_parts: how many (more than one for calls of few
-// blocks), 0 where the two kernels are faster (traj_bytes: their trajectories);
-// dar_fused_patterns: the patterns of one launch, 0 where paths of up to `longest`
-// links, or a launch of one pattern, do not fit it
+// The patterns of one launch of the one-kernel form, 0 where paths of up to
+// `longest` links, or a launch of one pattern, do not fit it.
 int32_t dar_fused_patterns(bool f64, int32_t n_paths, int32_t longest, int32_t H, int32_t H_speed,
                            int32_t K);
-int32_t dar_parts(bool f64, int32_t n_paths, int32_t longest, int32_t H, int32_t K,
-                  int32_t n_patterns, int32_t most_days, size_t part_bytes, size_t traj_bytes);
-size_t dar_part_bytes(bool f64, int32_t n_paths, int64_t n_pairs, int32_t H, int32_t K,
-                      int32_t n_patterns);
+// How a call takes that form: patterns of a launch (0: the two kernels serve it),
+// the parts that each pattern's days are split into, bytes of their sums (at most
+// `limit` and 64 MiB)
+struct DarSplit {
+  int32_t per_launch = 0;
+  std::vector<int32_t> parts;
+  size_t scratch = 0;
+};
+DarSplit dar_split(bool f64, int32_t n_paths, int64_t n_pairs, int32_t longest, int32_t H,
+                   int32_t H_speed, int32_t K, int32_t n_patterns, const int32_t* pattern_ptr,
+                   size_t limit);
+// dar_from_speeds for several patterns (pattern_ptr host [n_patterns+1]; Rr
+// [n_patterns][K][H][n_pairs], cost [n_patterns][H][n_paths] or nullptr)
 hipError_t dar_ratios(bool f64, int32_t n_paths, const int32_t* path_ptr, const int32_t* path_link,
                       int64_t n_pairs, int32_t longest, int32_t L, const void* len,
                       const void* speed, int32_t n_patterns, const int32_t* pattern_ptr,
                       int32_t H_speed, double dt, int32_t H, int32_t K, void* Rr, void* cost,
-                      int32_t n_parts, void* parts, hipStream_t s);
+                      const DarSplit& split, void* scratch, hipStream_t s);
 // cost[T][n_paths] = day mean of the path travel times for departures at t*dt;
 // partial = FP64 scratch [ceil(n_days/per_slice)][n_paths][T], per_slice % 4 == 0
 hipError_t path_costs(bool f64, int32_t n_paths, const int32_t* path_ptr, const int32_t* path_link,

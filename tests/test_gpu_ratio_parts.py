@@ -50,3 +50,31 @@ def test_parts_match_oracle(monkeypatch, f64, limit, lens, H, K, sizes, costs):
             co = orc.path_costs(ptr, link, si.link_len, sp, si.dt, H, walk=walk)
             err = np.abs(cost[q].cpu().numpy() - co) / np.maximum(co, 1.0)
             assert np.max(err) <= (1e-13 if f64 else 2e-7)
+
+
+@pytest.mark.parametrize("f64", [True, False])
+@pytest.mark.parametrize("lens,H,K,sizes", [
+    ((1, 7, 20), 24, 6, (200, 3, 77)),            # parts in some patterns of a launch
+    ((20, 9), 100, 3, (365, 340, 64, 1, 500)),    # blocks for all patterns, few for one
+    ((30, 70), 24, 12, (365, 24, 100)),           # many segments
+    ((5,) * 9, 288, 16, (96,) * 18),              # more patterns than a launch
+])
+def test_pattern_has_the_same_bits_alone(f64, lens, H, K, sizes):
+    """In a call of its own, and without costs."""
+    say("ratio parts alone", f64, lens, H, K, sizes)
+    rng = np.random.default_rng(53)
+    n_links = 30
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    link = dev(rng.integers(0, n_links, ptr[-1]), torch.int32)
+    t = torch.float64 if f64 else torch.float32
+    D = sum(sizes)
+    dptr = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    length, speed = dev(rng.random(n_links) + 0.2, t), dev(rng.random((D, n_links, H)) + 0.3, t)
+    paths = dev(ptr, torch.int32), link, length
+    Rr, cost = dode.dode_dar_patterns_from_speeds(*paths, speed, dptr, 1440.0 / H, H, K, with_costs=True)
+    for q in range(len(sizes)):
+        sp = speed[dptr[q]:dptr[q + 1]].contiguous()
+        Rq, cq = dode.dode_dar_costs_from_speeds(*paths, sp, 1440.0 / H, H, K)
+        Rn = dode.dode_dar_from_speeds(*paths, sp, 1440.0 / H, H, K)
+        torch.cuda.synchronize()
+        assert torch.equal(Rr[q], Rq) and torch.equal(cost[q], cq) and torch.equal(Rr[q], Rn)
